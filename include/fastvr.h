@@ -173,7 +173,8 @@ fastvr_status fastvr_chunk_attn_ring_step(const void* q_new, const void* k_new, 
  *                                                plane 1 -D_i
  * Mask arguments (chunk_len, q_chunk_offset, window_chunks) and scale are those
  * of the forward call that produced o and lse.  Two kernels run in order on
- * `stream`; sums run in a fixed order, so results are reproducible bit for bit.
+ * `stream` (row statistics, then all gradients).  Each sum runs in a fixed order,
+ * or as two such parts added into a zero, so results are reproducible bit for bit.
  *
  * Preconditions (else FASTVR_ERR_INVALID_ARGUMENT unless noted):
  *  - q, k, v, dout, o, dq, dk, dv non-NULL and 16-byte aligned (q, dout, o, dq

@@ -851,7 +851,8 @@ hipError_t launch_t(const Params& p, bool ring, int64_t n_items, const ItemLists
   return hipGetLastError();
 }
 
-// CU count of the current device, queried once per device (0 if it cannot be read)
+}  // namespace
+
 int device_cu_count() {
   constexpr int kMaxDevices = 64;
   static std::atomic<int> cus[kMaxDevices];  // 0: not queried yet, -1: query failed
@@ -868,8 +869,6 @@ int device_cu_count() {
   }
   return n > 0 ? n : 0;
 }
-
-}  // namespace
 
 hipError_t launch_chunk_attn_fwd(const FwdArgs& a, hipStream_t stream) {
   const FwdGrid g = fwd_grid(a.B, a.H, a.nq, a.chunk_len > a.nkv ? a.nkv : a.chunk_len);

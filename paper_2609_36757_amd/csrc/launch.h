@@ -49,6 +49,9 @@ constexpr int64_t kMaxFwdItems = (int64_t(1) << 32) / kFwdThreads - 1;
 // 32-bit buffer offsets of a 256-row tile: token strides stay below 2^22 elements
 constexpr int64_t kMaxTokenStride = int64_t(1) << 22;
 
+// CU count of the current device, queried once per device (0 if it cannot be read).
+int device_cu_count();
+
 FwdGrid fwd_grid(int64_t B, int64_t H, int64_t nq, int64_t chunk_len);
 hipError_t launch_chunk_attn_fwd(const FwdArgs& a, hipStream_t stream);
 
@@ -71,15 +74,14 @@ struct BwdArgs {
 };
 
 struct BwdGrid {
-  FwdGrid q;               // dQ kernel: query tiles, as in the forward
+  FwdGrid q;               // dQ units: query tiles, as in the forward
   int64_t n_kchunks;       // key chunks of the key range
   int64_t kblocks_full;    // key blocks of a full chunk
   int64_t kblocks_last;    // key blocks of the last (possibly ragged) chunk
-  int64_t n_kv_items;      // workgroups of the dK/dV kernel
+  int64_t n_kv_items;      // dK/dV units
 };
 
-constexpr int kBwdDqThreads = 512;   // 8 wave64, 32 queries each
-constexpr int kBwdDkvThreads = 512;  // 8 wave64: 4 pairs, 32 keys each
+constexpr int kBwdThreads = 512;  // 8 wave64: 32 queries each (dQ), or 4 pairs of 32 keys (dK/dV)
 constexpr int kBwdKeysPerItem = 128;
 
 BwdGrid bwd_grid(int64_t B, int64_t H, int64_t nq, int64_t nkv, int64_t chunk_len);

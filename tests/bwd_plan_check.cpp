@@ -1,0 +1,117 @@
+// CPU check of the backward's work plan (csrc/bwd_plan.h): over seeded shapes,
+// every (kind, chunk, batch * head, block, half) is decoded from exactly one
+// unit index, the halves of a split tile every streamed tile once, classes are
+// ordered longest first, and the grouped makespan equals a plain simulation.
+#include "bwd_plan.h"
+
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+#include <set>
+#include <tuple>
+#include <vector>
+
+using namespace fastvr;
+
+#define CHECK(x)                                              \
+  do {                                                        \
+    if (!(x)) {                                               \
+      std::printf("line %d: %s failed\n", __LINE__, #x);      \
+      std::exit(1);                                           \
+    }                                                         \
+  } while (0)
+
+static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+static BwdShape make(int64_t bh, int64_t nq, int64_t nkv, int64_t L, int64_t off, int64_t W) {
+  if (L > nkv) L = nkv;
+  BwdShape s{};
+  s.bh = bh;
+  s.n_qchunks = nq > 0 ? cdiv(nq, L) : 0;
+  if (nq > 0) {
+    s.tiles_last = cdiv(nq - (s.n_qchunks - 1) * L, 256);
+    s.tiles_full = s.n_qchunks > 1 ? cdiv(L, 256) : s.tiles_last;
+  }
+  s.n_kchunks = cdiv(nkv, L);
+  s.kblocks_last = cdiv(nkv - (s.n_kchunks - 1) * L, 128);
+  s.kblocks_full = s.n_kchunks > 1 ? cdiv(L, 128) : s.kblocks_last;
+  s.chunk_len = L;
+  s.q_chunk_offset = off;
+  s.window = W;
+  s.nq = nq;
+  s.nkv = nkv;
+  return s;
+}
+
+static void check(const BwdShape& s, int n_cu) {
+  BwdPlan p;
+  const int64_t n = bwd_plan(s, n_cu, &p);
+  CHECK(p.n_classes >= 1 && p.n_classes <= kBwdMaxClasses && p.first[0] == 0 && p.first[p.n_classes] == n);
+  CHECK((p.q_split == 1 || p.q_split == 2) && (p.kv_split == 1 || p.kv_split == 2));
+  std::set<std::tuple<int, int64_t, int64_t, int64_t, int64_t>> seen;
+  int64_t prev = INT64_MAX;
+  for (int k = 0; k < p.n_classes; ++k) {
+    const bool kv = p.is_kv[k] != 0;
+    const int64_t split = kv ? p.kv_split : p.q_split, last = (kv ? s.n_kchunks : s.n_qchunks) - 1;
+    const int64_t blocks = kv ? (p.c0[k] == last ? s.kblocks_last : s.kblocks_full)
+                              : (p.c0[k] == last ? s.tiles_last : s.tiles_full);
+    int64_t longest = 0;
+    for (int64_t u = p.first[k]; u < p.first[k + 1]; ++u) {
+      int64_t r = u - p.first[k];
+      const int64_t per_bh = blocks * split, per_c = per_bh * s.bh;
+      const int64_t c = p.c0[k] + r / per_c;
+      CHECK(r / per_c < p.nc[k]);
+      r %= per_c;
+      const int64_t bh = r / per_bh, t = r % per_bh / split, half = r % split;
+      CHECK(c <= last && bh < s.bh && half < split);
+      CHECK(seen.insert({kv ? 1 : 0, c, bh, half, t}).second);
+      longest = std::max(longest, kv ? bwd_kv_cost(bwd_kv_tiles(s, c), split) : bwd_q_cost(bwd_q_tiles(s, c), split));
+    }
+    CHECK(longest <= prev || s.n_qchunks > 8);  // grouped chunks may be unequal
+    prev = longest;
+  }
+  const int64_t q_units = s.n_qchunks ? s.bh * p.q_split * (s.tiles_last + s.tiles_full * (s.n_qchunks - 1)) : 0;
+  const int64_t kv_units = s.bh * p.kv_split * (s.kblocks_last + s.kblocks_full * (s.n_kchunks - 1));
+  CHECK(n == q_units + kv_units && (int64_t)seen.size() == n);
+}
+
+int main() {
+  std::mt19937_64 rng(7);
+  auto pick = [&](int64_t lo, int64_t hi) { return lo + (int64_t)(rng() % (uint64_t)(hi - lo + 1)); };
+  int cases = 0;
+  check(make(2, 1024, 1024, 256, 0, -1), 256), ++cases;
+  check(make(12, 18720, 18720, 3120, 0, -1), 256), ++cases;
+  check(make(2, 0, 300, 100, 0, -1), 256), ++cases;
+  check(make(1, 1, 1, 5, 0, -1), 256), ++cases;
+  check(make(2, 5000, 5000, 1, 0, 3), 256), ++cases;  // thousands of chunks
+  for (int i = 0; i < 300; ++i) {
+    const int64_t L = pick(1, 700), nkv = pick(1, 4000), W = pick(-1, 4);
+    const int64_t off = std::min<int64_t>(pick(0, 3), (nkv - 1) / std::min(L, nkv));
+    const int64_t room = nkv - off * std::min(L, nkv);
+    check(make(pick(1, 24), pick(1, room), nkv, L, L > nkv ? 0 : off, W), i % 3 ? 256 : (int)pick(1, 256));
+    ++cases;
+  }
+  // the splits that tests/test_gpu_bwd_split.py runs
+  const BwdShape gpu[5] = {make(8, 1616, 1616, 230, 0, -1), make(2, 300, 900, 300, 2, -1), make(2, 1537, 1537, 500, 0, -1),
+                           make(1, 2105, 2105, 100, 0, -1), make(1, 1300, 3900, 1300, 2, 0)};
+  for (int i = 0; i < 5; ++i) {
+    BwdPlan p;
+    bwd_plan(gpu[i], 256, &p);
+    CHECK(p.q_split == 2 && p.kv_split == (i < 2 ? 1 : 2));
+  }
+  // the grouped schedule against CU-by-CU simulation
+  for (int i = 0; i < 200; ++i, ++cases) {
+    BwdClass cls[kBwdMaxClasses];
+    const int n = (int)pick(1, kBwdMaxClasses), cu = (int)pick(1, 256);
+    std::vector<int64_t> load(cu, 0);
+    int64_t cost = pick(50, 400);
+    for (int k = 0; k < n; ++k) {
+      cls[k] = BwdClass{cost, pick(1, 300), 0, 1, 0};
+      cost -= std::min(cost - 1, pick(0, 12));
+      for (int64_t u = 0; u < cls[k].units; ++u) *std::min_element(load.begin(), load.end()) += cls[k].cost;
+    }
+    CHECK(bwd_makespan(cls, n, cu) == *std::max_element(load.begin(), load.end()));
+  }
+  std::printf("%d cases ok\n", cases);
+  return 0;
+}
