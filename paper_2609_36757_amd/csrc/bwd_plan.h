@@ -18,18 +18,14 @@
 
 #include <algorithm>
 
+#include "class_plan.h"
+
 namespace fastvr {
 
-constexpr int kBwdMaxClasses = 32;
-
-// Passed by value as a kernel argument.  Class k holds units first[k] ..
-// first[k + 1] - 1: chunks c0[k] .. c0[k] + nc[k] - 1 of one kind.
+// Passed by value as a kernel argument.
 struct BwdPlan {
-  int32_t n_classes;
+  ClassTable tab;             // kind 0: dQ units, 1: dK/dV units
   int32_t q_split, kv_split;  // parts per unit (1 or 2)
-  int32_t c0[kBwdMaxClasses], nc[kBwdMaxClasses];
-  int32_t is_kv[kBwdMaxClasses];
-  int32_t first[kBwdMaxClasses + 1];
 };
 
 // The call's decomposition (see FwdGrid / BwdGrid).
@@ -71,102 +67,22 @@ inline int64_t bwd_kv_cost(int64_t tiles, int64_t split) {
   return 3 * ((tiles + split - 1) / split) + (split > 1 ? kBwdSplitUnitCost : kBwdUnitCost);
 }
 
-struct BwdClass {
-  int64_t cost, units;
-  int32_t c0, nc, is_kv;
-};
-
-// The classes of one kind in chunk order (per-unit cost of a class: its
-// longest chunk's).  Runs of equal chunks share a class; with more runs than
-// `room` allows, neighbouring chunks are grouped.  The last chunk, whose tile
-// count may differ, is a class of its own.  Returns the number of classes.
-inline int bwd_classes(const BwdShape& s, bool kv, int64_t split, int room, BwdClass* out) {
+// The classes of one kind in chunk order.
+inline int bwd_classes(const BwdShape& s, bool kv, int64_t split, WorkClass* out) {
   const int64_t n = kv ? s.n_kchunks : s.n_qchunks;
   const int64_t per = (kv ? s.kblocks_full : s.tiles_full) * s.bh * split;
   const int64_t per_last = (kv ? s.kblocks_last : s.tiles_last) * s.bh * split;
-  auto cost = [&](int64_t c) {
+  return make_classes(n, per, per_last, kv ? 1 : 0, kMaxClasses / 2, out, [&](int64_t c) {
     return kv ? bwd_kv_cost(bwd_kv_tiles(s, c), split) : bwd_q_cost(bwd_q_tiles(s, c), split);
-  };
-  if (n <= 0) return 0;
-  int k = 0;
-  const int64_t body = n - 1;
-  // grouping step: 1 (merge equal neighbours only) unless that needs too many classes
-  for (int64_t step = 1;; step = std::max<int64_t>(2 * step, (body + room - 2) / (room - 1))) {
-    k = 0;
-    bool fits = true;
-    for (int64_t c = 0; c < body; c += step) {
-      const int64_t nc = std::min(step, body - c);
-      // longest of the group: costs are monotone in the chunk up to the window's ends
-      const int64_t w = std::max(std::max(cost(c), cost(c + nc - 1)), cost(c + nc / 2));
-      if (k > 0 && out[k - 1].cost == w) {
-        out[k - 1].nc += (int32_t)nc;
-        out[k - 1].units += nc * per;
-      } else if (k < room - 1) {
-        out[k++] = BwdClass{w, nc * per, (int32_t)c, (int32_t)nc, kv ? 1 : 0};
-      } else {
-        fits = false;
-        break;
-      }
-    }
-    if (fits) break;
-  }
-  out[k++] = BwdClass{cost(n - 1), per_last, (int32_t)(n - 1), 1, kv ? 1 : 0};
-  return k;
+  });
 }
 
 // Both kinds' classes, longest first.
-inline int bwd_sorted_classes(const BwdShape& s, int64_t q_split, int64_t kv_split, BwdClass* out) {
-  int n = bwd_classes(s, true, kv_split, kBwdMaxClasses / 2, out);
-  n += bwd_classes(s, false, q_split, kBwdMaxClasses / 2, out + n);
-  std::stable_sort(out, out + n, [](const BwdClass& a, const BwdClass& b) { return a.cost > b.cost; });
+inline int bwd_sorted_classes(const BwdShape& s, int64_t q_split, int64_t kv_split, WorkClass* out) {
+  int n = bwd_classes(s, true, kv_split, out);
+  n += bwd_classes(s, false, q_split, out + n);
+  sort_classes(out, n);
   return n;
-}
-
-// Makespan of dispatching the classes in order on n_cu CUs (each unit on the CU
-// that frees up first), with CUs of equal load kept as one group.
-inline int64_t bwd_makespan(const BwdClass* cls, int n, int n_cu) {
-  constexpr int kMaxGroups = 512;
-  int64_t load[kMaxGroups];
-  int count[kMaxGroups];
-  int head = 0, tail = 1;  // groups head .. tail - 1, ascending load
-  load[0] = 0;
-  count[0] = n_cu;
-  for (int k = 0; k < n; ++k) {
-    int64_t m = cls[k].units;
-    while (m > 0) {
-      const int64_t l = load[head] + cls[k].cost;
-      int take = count[head];
-      if (m < take) {
-        take = (int)m;
-        count[head] -= take;
-      } else {
-        ++head;
-      }
-      m -= take;
-      // insert (l, take)
-      int i = tail;
-      while (i > head && load[i - 1] > l) --i;
-      if (i > head && load[i - 1] == l) {
-        count[i - 1] += take;
-        continue;
-      }
-      if (tail == kMaxGroups) {  // close the gap at the front
-        std::copy(load + head, load + tail, load);
-        std::copy(count + head, count + tail, count);
-        tail -= head;
-        i -= head;
-        head = 0;
-      }
-      for (int j = tail; j > i; --j) {
-        load[j] = load[j - 1];
-        count[j] = count[j - 1];
-      }
-      load[i] = l;
-      count[i] = take;
-      ++tail;
-    }
-  }
-  return load[tail - 1];
 }
 
 // Units per CU up to which the split choices are simulated.  At 3.5 (9 chunks of
@@ -176,16 +92,16 @@ constexpr int64_t kBwdSplitMaxRounds = 4;
 
 // Fills the plan; returns the number of units (the grid).
 inline int64_t bwd_plan(const BwdShape& s, int n_cu, BwdPlan* p) {
-  BwdClass cls[kBwdMaxClasses], best[kBwdMaxClasses];
+  WorkClass cls[kMaxClasses], best[kMaxClasses];
   int n = bwd_sorted_classes(s, 1, 1, best);
   p->q_split = p->kv_split = 1;
   int64_t units = 0;
   for (int k = 0; k < n; ++k) units += best[k].units;
   if (n_cu > 0 && n_cu <= 256 && units <= kBwdSplitMaxRounds * n_cu) {
-    int64_t span = bwd_makespan(best, n, n_cu);
+    int64_t span = class_makespan(best, n, n_cu);
     for (int opt = 1; opt < 4; ++opt) {
       const int m = bwd_sorted_classes(s, (opt & 1) ? 2 : 1, (opt & 2) ? 2 : 1, cls);
-      const int64_t t = bwd_makespan(cls, m, n_cu);
+      const int64_t t = class_makespan(cls, m, n_cu);
       if (25 * t < 24 * span) {  // 4% at least: the model is no better than that
         span = t;
         n = m;
@@ -195,17 +111,7 @@ inline int64_t bwd_plan(const BwdShape& s, int n_cu, BwdPlan* p) {
       }
     }
   }
-  p->n_classes = n;
-  units = 0;
-  for (int k = 0; k < n; ++k) {
-    p->first[k] = (int32_t)units;
-    p->c0[k] = best[k].c0;
-    p->nc[k] = best[k].nc;
-    p->is_kv[k] = best[k].is_kv;
-    units += best[k].units;
-  }
-  p->first[n] = (int32_t)units;
-  return units;
+  return fill_table(best, n, &p->tab);
 }
 
 }  // namespace fastvr

@@ -200,18 +200,6 @@ __device__ __forceinline__ void pack_bf16(const f32x16 (&a)[2], u32x4 (&f)[4]) {
   f[3] = f1[1];
 }
 
-// Workgroups go to the 8 XCDs round-robin; within each round of 256 workgroups
-// of a class (the last one may be shorter), each XCD gets consecutive units
-// (neighbouring tiles of one stream share its L2).  i: index within the class of
-// n units.  Rounds over all units instead would give whole XCDs to one class.
-__device__ __forceinline__ int xcd_unit(int i, int n) {
-  constexpr int kRound = 256;
-  const int r0 = i / kRound * kRound, w = i - r0;
-  const int m = (n - r0 < kRound) ? n - r0 : kRound;  // units of this round
-  const int x = w & 7, per = m >> 3, rem = m & 7;
-  return r0 + x * per + (x < rem ? x : rem) + (w >> 3);
-}
-
 // A wave's 32 gradient rows (accumulators acc: lane n holds dims dm * 32 + 8 g +
 // 4 hh + 0..3 of row n, times sc) into rows row0 .. of out (row stride st
 // elements), of which `rows` are valid: stored.
@@ -905,21 +893,22 @@ __device__ __forceinline__ void dkv_unit(const BwdParams& p, int ck, int bh, int
 // (6 chunks of 3120, 12 heads: 3.70 against 3.79 ms).
 template <int D, bool SPLIT>
 __global__ __launch_bounds__(kBwdThreads) void chunk_attn_bwd_kernel(const BwdParams p, const BwdPlan plan) {
+  const ClassTable& tab = plan.tab;
   constexpr int kDqLds = 2 * kStages * TileDma<D, kDqWaves>::kElems * 2;
   constexpr int kLds = kDkvLds<D> > kDqLds ? kDkvLds<D> : kDqLds;
   static_assert(kLds >= (kBwdThreads / 64) * 32 * D * 4, "add_rows keeps 32 rows per wave");
   __shared__ __attribute__((aligned(16))) uint16_t smem[kLds / 2];
   const int u = p.unit_base + (int)blockIdx.x;
   int k = 0;
-  while (k + 1 < plan.n_classes && u >= plan.first[k + 1]) ++k;
+  while (k + 1 < tab.n && u >= tab.first[k + 1]) ++k;
   // unit -> (chunk, batch * head, tile or key block, half) of its class; the
   // halves are neighbours, so they mostly share an XCD and its L2
-  const bool kv = plan.is_kv[k] != 0;
+  const bool kv = tab.kind[k] != 0;
   const int split = SPLIT ? (kv ? plan.kv_split : plan.q_split) : 1;
-  const int c0 = plan.c0[k], last = (kv ? p.n_kchunks : p.n_local_chunks) - 1;
+  const int c0 = tab.c0[k], last = (kv ? p.n_kchunks : p.n_local_chunks) - 1;
   const int blocks = kv ? (c0 == last ? p.kblocks_last : p.kblocks_full) : (c0 == last ? p.tiles_last : p.tiles_full);
   const int per_bh = blocks * split, per_c = p.B * p.H * per_bh;
-  int r = xcd_unit(u - plan.first[k], plan.first[k + 1] - plan.first[k]);
+  int r = xcd_unit(u - tab.first[k], tab.first[k + 1] - tab.first[k]);
   const int ci = r / per_c;
   r -= ci * per_c;
   const int bh = r / per_bh;

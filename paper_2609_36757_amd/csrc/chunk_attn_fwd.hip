@@ -9,8 +9,11 @@
 //
 // Work decomposition: one workgroup (8 wave64, 512 threads) per
 // (batch, head, query chunk, 256-row query tile); tiles never straddle a chunk.
-// Items are dispatched longest first; when they are few per CU and uneven, the
-// host instead packs them into one list per CU and launches one workgroup per
+// Items are dispatched longest first, a class of equal items at a time with the
+// classes spread over all XCDs (5003 tokens in chunks of 1365, W = 2, 16 heads,
+// d = 64: 103.7 -> 84 us against rounds of 256 that gave whole XCDs to one class);
+// calls that leave CUs idle run 128-row items instead (see there); when items are
+// few per CU and uneven, the host instead packs them into one list per CU and launches one workgroup per
 // CU that runs its list (item_lists.h).  Each wave owns 32 query rows.  Scores are computed transposed,
 // S^T = K Q^T, with v_mfma_f32_32x32x16_bf16: the accumulator puts one query per
 // lane (column) and 16 keys per lane (rows), so row max and row sum are in-lane
@@ -47,6 +50,7 @@
 
 #include <atomic>
 
+#include "fwd_plan.h"
 #include "gfx950_ops.h"
 #include "item_lists.h"
 #include "launch.h"
@@ -89,6 +93,10 @@ constexpr int kStages = 3;                // LDS buffers per operand
 #ifndef FASTVR_VALU_PER
 #define FASTVR_VALU_PER 4
 #endif
+//  FASTVR_HALF_VALU_PER  128-row items: softmax instructions placed after each S MFMA (of 24)
+#ifndef FASTVR_HALF_VALU_PER
+#define FASTVR_HALF_VALU_PER 5
+#endif
 #ifndef FASTVR_DMA_SPLIT
 #define FASTVR_DMA_SPLIT 1
 #endif
@@ -126,10 +134,8 @@ __device__ __forceinline__ int vswz(int u) {
   return D >= 128 ? (((u & 1) * 6) ^ ((u >> 1) * 12)) : 2 * u;
 }
 
-// Item index vi -> (local query chunk, batch*head, tile).  Items are ordered by
-// query chunk, last chunk first: under the causal mask later chunks see at
-// least as many keys, so the longest items start first.  (The host's item-list
-// planner decodes item indices the same way.)
+// Item index vi of an item list -> (local query chunk, batch*head, tile), last
+// chunk first.  (The host's item-list planner decodes item indices the same way.)
 __device__ __forceinline__ void decode_item(const Params& p, int vi, int& cl, int& bh, int& t) {
   const int BH = p.B * p.H;
   const int n_last = BH * p.tiles_last;
@@ -148,18 +154,22 @@ __device__ __forceinline__ void decode_item(const Params& p, int vi, int& cl, in
   }
 }
 
-// blockIdx -> item index.  Workgroups are handed to the 8 XCDs round-robin;
-// within each full round of 256 workgroups the mapping gives XCD x a run of 32
-// consecutive items (same batch, head and chunk, i.e. the same K/V stream) so
-// they share that XCD's L2.
-__device__ __forceinline__ int item_of_block(const Params& p, int i) {
-  constexpr int kRound = 256;
-  const int full = (p.n_items / kRound) * kRound;
-  if (i < full) {
-    const int r = i / kRound, w = i % kRound;
-    return r * kRound + (w & 7) * 32 + (w >> 3);
-  }
-  return i;
+// blockIdx -> (local query chunk, batch * head, tile) through the call's class
+// table (class_plan.h).  Workgroups are handed to the 8 XCDs round-robin; within
+// a class of equal items each XCD gets runs of 32 consecutive ones (same batch,
+// head and chunk, i.e. the same K/V stream), which share its L2.
+__device__ __forceinline__ void decode_block(const Params& p, const ClassTable& tab, int& cl, int& bh, int& t) {
+  const int u = blockIdx.x;
+  int k = 0;
+  while (k + 1 < tab.n && u >= tab.first[k + 1]) ++k;
+  const int c0 = tab.c0[k];
+  const int tiles = c0 == p.n_local_chunks - 1 ? p.tiles_last : p.tiles_full, per = p.B * p.H * tiles;
+  int r = xcd_unit(u - tab.first[k], tab.first[k + 1] - tab.first[k]);
+  const int ci = r / per;
+  r -= ci * per;
+  cl = c0 + ci;
+  bh = r / tiles;
+  t = r - bh * tiles;
 }
 
 // SPLIT: the matrix-core slot takes only each lane's row maximum of the fresh
@@ -384,7 +394,7 @@ struct Attn {
   // outside the visible interval): running maximum m (log2 domain), alpha =
   // 2^(m_old - m), and s <- s * c - m in place, ready for exp2.
   template <bool MASK>
-  __device__ __forceinline__ void row_stats(int n_valid) {
+  __device__ __forceinline__ void row_stats(f32x16 (&s)[kKB], int n_valid) {
     constexpr float kInf = __builtin_inff();
     // keys of this lane: mb * 32 + 8 * (v >> 2) + (v & 3) + 4 * hh; the limit is
     // made opaque so that the compares are not shared with another call site
@@ -460,11 +470,11 @@ struct Attn {
       for (int v = 0; v < 16; ++v) s[mb][v] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[mb][v], c, nm));
   }
 
-  // The rest of the online softmax once row_stats has run: P = exp2(t) rounded
-  // to bf16 fragments, l = l * alpha + rowsum(P), O *= alpha.  With split
-  // statistics (EXP_DONE) the exp2 was already taken by row_max_finish_exp.
+  // P = exp2(t) rounded to bf16 fragments, l = l * alpha + rowsum(P), once
+  // row_stats has run.  With split statistics (EXP_DONE) the exp2 was already
+  // taken by row_max_finish_exp.
   template <bool EXP_DONE = false>
-  __device__ __forceinline__ void softmax_rest() {
+  __device__ __forceinline__ void exp_sum_pack(f32x16 (&s)[kKB]) {
     if (!EXP_DONE) {
 #pragma unroll
       for (int mb = 0; mb < kKB; ++mb)
@@ -484,10 +494,19 @@ struct Attn {
       for (int r = 0; r < 8; ++r) b[r] = (__bf16)s[g >> 1][8 * (g & 1) + r];
       pf[g] = __builtin_bit_cast(u32x4, b);
     }
+  }
+  // O *= alpha, when some row's maximum grew
+  __device__ __forceinline__ void rescale() {
     if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {
 #pragma unroll
       for (int dm = 0; dm < D / 32; ++dm) o[dm] *= alpha;
     }
+  }
+  // The rest of the online softmax once row_stats has run.
+  template <bool EXP_DONE = false>
+  __device__ __forceinline__ void softmax_rest() {
+    exp_sum_pack<EXP_DONE>(s);
+    rescale();
   }
 
   // One matrix-core slot: S^T(tile in st_k) = K Q^T (QK), then
@@ -548,7 +567,7 @@ struct Attn {
       if (SPLIT)
         row_max_partial();
       else
-        row_stats<false>(kBK);
+        row_stats<false>(s, kBK);
     }
 #if FASTVR_SCHED
     if (PV) {
@@ -581,38 +600,25 @@ struct Attn {
   // taken here rather than in the matrix-core slot.
   __device__ __forceinline__ void softmax_last(int last_valid) {
     if (last_valid < kBK)
-      row_stats<true>(last_valid);
+      row_stats<true>(s, last_valid);
     else
-      row_stats<false>(kBK);
+      row_stats<false>(s, kBK);
     softmax_rest();
   }
 };
 
-// One work item (a query tile of one batch, head and query chunk) from its
-// decode to its epilogue, run by the whole workgroup; smem is the workgroup's
-// LDS.  Waves without query rows leave before the epilogue.
-template <int D, bool NEG, bool RING, bool SPLIT = false>
-__device__ __forceinline__ void fwd_item(const Params& p, int vi, uint16_t* smem) {
-  using A = Attn<D, NEG, RING, SPLIT>;
-  A a;
-  a.ks = smem;
-  a.vs = smem + kStages * A::kStage;
-  const int tid = threadIdx.x;
-  a.lane = tid & 63;
-  a.wave = tid >> 6;
-  a.n = a.lane & 31;
-  a.hh = a.lane >> 5;
-  a.c = p.c;
-  const int group = a.wave >> 2;  // 0: waves 0-3, 1: waves 4-7 (one wave of each per SIMD)
-
-  int cl, bh, t;
-  decode_item(p, vi, cl, bh, t);
-  const int b = bh / p.H, h = bh - (bh / p.H) * p.H;
+// Item (cl, bh, t): batch, head, its query rows q0 .. (below q_end), and the key
+// interval, tensors and strides in `a`.
+template <typename A, int D, bool RING>
+__device__ __forceinline__ void item_rows(const Params& p, int cl, int bh, int t, int tile_rows, A& a, int& b, int& h,
+                                          int& q0, int& q_end) {
+  b = bh / p.H;
+  h = bh - b * p.H;
 
   const int L = p.chunk_len;
   const int chunk_q0 = cl * L;
-  const int q_end = (L < p.nq - chunk_q0) ? chunk_q0 + L : p.nq;
-  const int q0 = chunk_q0 + t * kBQ;
+  q_end = (L < p.nq - chunk_q0) ? chunk_q0 + L : p.nq;
+  q0 = chunk_q0 + t * tile_rows;
   const int cg = p.q_chunk_offset + cl;  // global chunk of this query tile
   a.lo = (p.window >= 0 && cg > p.window) ? (cg - p.window) * L : 0;
   a.hi = (L < p.nkv - cg * L) ? (cg + 1) * L : p.nkv;
@@ -630,6 +636,77 @@ __device__ __forceinline__ void fwd_item(const Params& p, int vi, uint16_t* smem
     a.n_seg = p.n_seg;
     a.n_last = p.nq;  // the new chunk: as many keys as queries
   }
+}
+
+// Fused append of a ring step: this workgroup's share of the new chunk's K and V
+// goes to ring slot new_slot (a slot no query of this call reads).
+__device__ __forceinline__ void ring_append(const Params& p, int D) {
+  const int64_t hd8 = (int64_t)p.H * D / 8;        // 16-byte units per token
+  const int64_t per_b = (int64_t)p.nq * hd8;        // units per batch row
+  const int64_t total = per_b * p.B;
+  const int64_t share = (total + p.n_items - 1) / p.n_items;
+  const int64_t u0 = (int64_t)blockIdx.x * share;
+  const int64_t u1 = (u0 + share < total) ? u0 + share : total;
+  for (int bb = 0; bb < p.B; ++bb) {
+    const int64_t lo_u = (u0 > bb * per_b) ? u0 : bb * per_b;
+    const int64_t hi_u = (u1 < (bb + 1) * per_b) ? u1 : (bb + 1) * per_b;
+    if (lo_u >= hi_u) continue;
+    const u32x4* ksrc = reinterpret_cast<const u32x4*>(p.k + (int64_t)bb * p.k_sb);
+    const u32x4* vsrc = reinterpret_cast<const u32x4*>(p.v + (int64_t)bb * p.v_sb);
+    const int64_t dst = (int64_t)bb * p.ring_sb + (int64_t)p.new_slot * p.ring_chunk * p.k_st;
+    u32x4* kd = reinterpret_cast<u32x4*>(p.rk + dst);
+    u32x4* vd = reinterpret_cast<u32x4*>(p.rv + dst);
+    for (int64_t u = lo_u - bb * per_b + threadIdx.x; u < hi_u - bb * per_b; u += kFwdThreads) {
+      kd[u] = ksrc[u];
+      vd[u] = vsrc[u];
+    }
+  }
+}
+
+// O of one query row: lane (row, hh) holds dims dm * 32 + 8 g + 4 hh + 0..3.
+template <int D>
+__device__ __forceinline__ void store_row(const Params& p, const f32x16 (&o)[D / 32], float inv, int b, int h, int row,
+                                          int hh) {
+  const int64_t oo = (int64_t)b * p.o_sb + (int64_t)row * p.o_st + (int64_t)h * D;
+#pragma unroll
+  for (int dm = 0; dm < D / 32; ++dm)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      f32x4 val;
+      val.x = o[dm][4 * g + 0] * inv;
+      val.y = o[dm][4 * g + 1] * inv;
+      val.z = o[dm][4 * g + 2] * inv;
+      val.w = o[dm][4 * g + 3] * inv;
+      const int64_t e = oo + dm * 32 + g * 8 + hh * 4;
+      if (p.o_bf16) {
+        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+        const bf16x4 r = {(__bf16)val.x, (__bf16)val.y, (__bf16)val.z, (__bf16)val.w};
+        *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(p.o) + e) = r;
+      } else {
+        *reinterpret_cast<f32x4*>(static_cast<float*>(p.o) + e) = val;
+      }
+    }
+}
+
+// One work item (a query tile of one batch, head and query chunk) from its
+// decode to its epilogue, run by the whole workgroup; smem is the workgroup's
+// LDS.  Waves without query rows leave before the epilogue.
+template <int D, bool NEG, bool RING, bool SPLIT = false>
+__device__ __forceinline__ void fwd_item(const Params& p, int cl, int bh, int t, uint16_t* smem) {
+  using A = Attn<D, NEG, RING, SPLIT>;
+  A a;
+  a.ks = smem;
+  a.vs = smem + kStages * A::kStage;
+  const int tid = threadIdx.x;
+  a.lane = tid & 63;
+  a.wave = tid >> 6;
+  a.n = a.lane & 31;
+  a.hh = a.lane >> 5;
+  a.c = p.c;
+  const int group = a.wave >> 2;  // 0: waves 0-3, 1: waves 4-7 (one wave of each per SIMD)
+
+  int b, h, q_end, q0;
+  item_rows<A, D, RING>(p, cl, bh, t, kBQ, a, b, h, q0, q_end);
   a.init_offsets();
 
   const int row = q0 + a.wave * 32 + a.n;
@@ -760,30 +837,7 @@ __device__ __forceinline__ void fwd_item(const Params& p, int vi, uint16_t* smem
   }
   barrier();
   if (active && group == 1) a.template mfma_slot<false, true, false>(0, st_cur);
-  if (RING) {
-    // fused append: this workgroup's share of the new chunk's K and V goes to
-    // ring slot new_slot (a slot no query of this call reads)
-    const int64_t hd8 = (int64_t)p.H * D / 8;        // 16-byte units per token
-    const int64_t per_b = (int64_t)p.nq * hd8;        // units per batch row
-    const int64_t total = per_b * p.B;
-    const int64_t share = (total + p.n_items - 1) / p.n_items;
-    const int64_t u0 = (int64_t)blockIdx.x * share;
-    const int64_t u1 = (u0 + share < total) ? u0 + share : total;
-    for (int bb = 0; bb < p.B; ++bb) {
-      const int64_t lo_u = (u0 > bb * per_b) ? u0 : bb * per_b;
-      const int64_t hi_u = (u1 < (bb + 1) * per_b) ? u1 : (bb + 1) * per_b;
-      if (lo_u >= hi_u) continue;
-      const u32x4* ksrc = reinterpret_cast<const u32x4*>(p.k + (int64_t)bb * p.k_sb);
-      const u32x4* vsrc = reinterpret_cast<const u32x4*>(p.v + (int64_t)bb * p.v_sb);
-      const int64_t dst = (int64_t)bb * p.ring_sb + (int64_t)p.new_slot * p.ring_chunk * p.k_st;
-      u32x4* kd = reinterpret_cast<u32x4*>(p.rk + dst);
-      u32x4* vd = reinterpret_cast<u32x4*>(p.rv + dst);
-      for (int64_t u = lo_u - bb * per_b + tid; u < hi_u - bb * per_b; u += kFwdThreads) {
-        kd[u] = ksrc[u];
-        vd[u] = vsrc[u];
-      }
-    }
-  }
+  if (RING) ring_append(p, D);
   if (!active) return;
 
   // epilogue: the two halves of the wave hold partial sums over disjoint keys
@@ -791,36 +845,19 @@ __device__ __forceinline__ void fwd_item(const Params& p, int vi, uint16_t* smem
   const float l_mine = swap_halves(a.l_run, &l_other);
   const float l_tot = l_mine + l_other;
   if (row < q_end) {
-    const float inv = 1.0f / l_tot;
-    const int64_t oo = (int64_t)b * p.o_sb + (int64_t)row * p.o_st + (int64_t)h * D;
-#pragma unroll
-    for (int dm = 0; dm < D / 32; ++dm)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        f32x4 val;
-        val.x = a.o[dm][4 * g + 0] * inv;
-        val.y = a.o[dm][4 * g + 1] * inv;
-        val.z = a.o[dm][4 * g + 2] * inv;
-        val.w = a.o[dm][4 * g + 3] * inv;
-        const int64_t e = oo + dm * 32 + g * 8 + a.hh * 4;
-        if (p.o_bf16) {
-          typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-          const bf16x4 r = {(__bf16)val.x, (__bf16)val.y, (__bf16)val.z, (__bf16)val.w};
-          *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(p.o) + e) = r;
-        } else {
-          *reinterpret_cast<f32x4*>(static_cast<float*>(p.o) + e) = val;
-        }
-      }
+    store_row<D>(p, a.o, 1.0f / l_tot, b, h, row, a.hh);
     if (a.hh == 0 && p.lse != nullptr)
       p.lse[((int64_t)b * p.H + h) * p.nq + row] = (a.m_run + __builtin_log2f(l_tot)) * kLn2;
   }
 }
 
-// One workgroup per item, dispatched in item order (longest first).
+// One workgroup per item, dispatched longest first.
 template <int D, bool NEG, bool RING>
-__global__ __launch_bounds__(kFwdThreads) void chunk_attn_fwd_kernel(const Params p) {
+__global__ __launch_bounds__(kFwdThreads) void chunk_attn_fwd_kernel(const Params p, const ClassTable tab) {
   __shared__ __attribute__((aligned(16))) uint16_t smem[Attn<D, NEG, RING>::kLdsElems];
-  fwd_item<D, NEG, RING>(p, item_of_block(p, blockIdx.x), smem);
+  int cl, bh, t;
+  decode_block(p, tab, cl, bh, t);
+  fwd_item<D, NEG, RING>(p, cl, bh, t, smem);
 }
 
 // One workgroup per CU, each running the items of its own list one after the
@@ -830,24 +867,221 @@ __global__ __launch_bounds__(kFwdThreads) void chunk_attn_fwd_list_kernel(const 
   __shared__ __attribute__((aligned(16))) uint16_t smem[Attn<D, NEG, false>::kLdsElems];
   const int g = blockIdx.x;
   for (int u = lst.start[g]; u < lst.start[g + 1]; ++u) {
-    fwd_item<D, NEG, false, true>(p, lst.item[u], smem);
+    int cl, bh, t;
+    decode_item(p, lst.item[u], cl, bh, t);
+    fwd_item<D, NEG, false, true>(p, cl, bh, t, smem);
     // every wave is done with the item's LDS stages before the next item's DMA
     barrier();
   }
 }
 
+// ------------------------------------------------------- 128-row items
+//
+// For calls whose 256-row items leave CUs idle: an item of 128 rows, in which
+// each SIMD's two waves share 32 query rows.  Wave a (0-3) owns the scores and
+// the softmax, wave a + 4 owns O: in step j the first runs S(j + 1) = K Q^T on
+// the matrix core between the vector-ALU instructions of tile j's softmax and
+// hands P(j) and alpha(j) over through LDS; the second runs O = O alpha(j - 1) +
+// V^T P^T(j - 1).  A key tile then takes a step of one wave's softmax instead
+// of two slots with a matrix-core and a vector-ALU share each.  Per row the
+// arithmetic and its order are those of the 256-row items, so the outputs are
+// the same bits.  K, V and P are double-buffered in LDS (K(j + 2) and V(j) are
+// in flight during step j): the tiles of calls this small come from L2.
+//
+// A key tile takes 1.28 us (head_dim 128) or 0.77 us (64) against 2.05 and 1.58 us
+// in a 256-row item on a chip that is not full: one chunk of 3000 tokens and 4
+// heads 71.6 -> 47.8 us, 4 x 256 tokens and 2 heads (d = 64) 23.4 -> 15.2 us.
+// At head_dim 128 the step is bound by LDS and the tile DMA: 240 KB of operand
+// and P traffic at 128 bytes per clock is 1900 cycles, and 12 DMA instructions
+// per O wave hold it for 1560 (giving the score waves half of K's, or either
+// role a higher priority, changed nothing); at 64 by the softmax of the score
+// wave.  Twice the K/V traffic per query row makes it 14% (11%) slower than
+// 256-row items on a full chip, so fwd_plan.h picks the height per call.
+static_assert(kHalfRows == 4 * 32, "32 rows per wave pair");
+
+template <int D>
+constexpr int kHalfP = 4 * kKG * 64;  // 16-byte units of P per buffer: [pair][key group][lane]
+template <int D>
+constexpr int kHalfLds = 2 * 2 * kBK * D * 2 + 2 * kHalfP<D> * 16 + 3 * kHalfRows * 4;  // bytes
+
+template <int D, bool NEG, bool RING>
+struct HalfAttn : Attn<D, NEG, RING> {
+  static constexpr int kN = D * kBK / 512;  // MFMAs of S or of P.V
+
+  // sn = K Q^T of the tile in K stage kst (QK), with the softmax of the scores
+  // sc (SM): fragments pf, alpha.  MASK: sc holds fewer than kBK visible keys.
+  template <bool QK, bool SM, bool MASK>
+  __device__ __forceinline__ void score_step(f32x16 (&sc)[kKB], f32x16 (&sn)[kKB], const char* kst, int n_valid) {
+    constexpr int kAhead = FASTVR_AHEAD < kN ? FASTVR_AHEAD : kN;
+    if (QK) {
+      u32x4 kf[kN];
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) kf[i] = this->read_k(kst, i);
+#pragma unroll
+      for (int i = 0; i < kN; ++i) {
+        if (i + kAhead < kN) kf[i + kAhead] = this->read_k(kst, i + kAhead);
+        const int kk = i / kKB, mb = i % kKB;
+        sn[mb] = (kk == 0) ? mfma32(kf[i], this->qf[kk], f32x16{}) : mfma32(kf[i], this->qf[kk], sn[mb]);
+      }
+    }
+    if (SM) {
+      this->template row_stats<MASK>(sc, n_valid);
+      this->exp_sum_pack(sc);
+    }
+    if (QK) {
+      __builtin_amdgcn_sched_group_barrier(SCHED_DS_READ, kAhead, 0);
+#pragma unroll
+      for (int i = 0; i < kN; ++i) {
+        __builtin_amdgcn_sched_group_barrier(SCHED_MFMA, 1, 0);
+        if (i + kAhead < kN) __builtin_amdgcn_sched_group_barrier(SCHED_DS_READ, 1, 0);
+        if (SM) __builtin_amdgcn_sched_group_barrier(SCHED_VALU, FASTVR_HALF_VALU_PER * 24 / kN, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+};
+
+template <int D, bool NEG, bool RING>
+__device__ __forceinline__ void fwd_half_item(const Params& p, int cl, int bh, int t, char* lds) {
+  using A = HalfAttn<D, NEG, RING>;
+  A a;
+  a.ks = reinterpret_cast<uint16_t*>(lds);
+  a.vs = a.ks + 2 * A::kStage;
+  u32x4* pex = reinterpret_cast<u32x4*>(a.vs + 2 * A::kStage);
+  float* alf = reinterpret_cast<float*>(pex + 2 * kHalfP<D>);  // [buffer][row]; the third one holds 1 / l
+  const int tid = threadIdx.x;
+  a.lane = tid & 63;
+  // scalar: the two roles branch apart and meet at barriers
+  a.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  a.n = a.lane & 31;
+  a.hh = a.lane >> 5;
+  a.c = p.c;
+  const int group = a.wave >> 2;  // 0: scores, 1: O
+  const int pair = a.wave & 3;
+
+  int b, h, q_end, q0;
+  item_rows<A, D, RING>(p, cl, bh, t, kHalfRows, a, b, h, q0, q_end);
+  a.init_offsets();
+  const int row0 = q0 + pair * 32, row = row0 + a.n;
+  const bool active = row0 < q_end;  // wave-uniform
+  const int n = a.n_tiles;
+  const int last_valid = a.hi - (a.lo + (n - 1) * kBK);
+  // the O waves, the less busy ones, issue all the DMA
+  if (group == 1) {
+    a.load_k(0, 0);
+    if (n > 1) a.load_k(1, 1);
+  }
+  if (group == 0) {
+    const int rows = q_end - row0;
+    const __amdgpu_buffer_rsrc_t rq = make_rsrc(p.q + (int64_t)b * p.q_sb + (int64_t)row0 * p.q_st + (int64_t)h * D,
+                                                rows > 0 ? (int64_t)rows * p.q_st * 2 : 0);
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk)
+      a.qf[kk] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                               rq, (uint32_t)(a.n * p.q_st + kk * 16 + a.hh * 8) * 2u, 0, 0));
+  }
+  wait_vmcnt<0>();
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+  barrier();
+  auto kst = [&](int j) { return reinterpret_cast<const char*>(a.ks + (j & 1) * A::kStage); };
+  if (group == 0) {
+    a.m_run = -__builtin_inff();
+    a.l_run = 0.f;
+    f32x16 s0[kKB], s1[kKB];
+    if (active) a.template score_step<true, false, false>(s1, s0, kst(0), kBK);
+    barrier();
+    // P(j) and alpha(j) to the O wave; end of step j
+    auto hand_over = [&](int j) {
+      if (active) {
+        u32x4* dst = pex + (j & 1) * kHalfP<D> + pair * kKG * 64 + a.lane;
+#pragma unroll
+        for (int g = 0; g < kKG; ++g) dst[g * 64] = a.pf[g];
+        if (a.hh == 0) alf[(j & 1) * kHalfRows + pair * 32 + a.n] = a.alpha;
+      }
+    };
+    auto step = [&](int j, f32x16(&sc)[kKB], f32x16(&sn)[kKB]) {
+      if (active) a.template score_step<true, true, false>(sc, sn, kst(j + 1), kBK);
+      hand_over(j);
+      barrier();
+    };
+    auto last = [&](f32x16(&sc)[kKB]) {
+      if (active) {
+        if (last_valid < kBK)
+          a.template score_step<false, true, true>(sc, sc, nullptr, last_valid);
+        else
+          a.template score_step<false, true, false>(sc, sc, nullptr, kBK);
+      }
+      hand_over(n - 1);
+    };
+    int j = 0;
+    for (; j + 2 < n; j += 2) {
+      step(j, s0, s1);
+      step(j + 1, s1, s0);
+    }
+    if (j + 1 < n) {
+      step(j, s0, s1);
+      last(s1);
+    } else {
+      last(s0);
+    }
+    float l_other;
+    const float l_mine = swap_halves(a.l_run, &l_other);
+    const float l_tot = l_mine + l_other;
+    if (active && a.hh == 0) alf[2 * kHalfRows + pair * 32 + a.n] = 1.0f / l_tot;
+    barrier();
+    if (active && a.hh == 0 && row < q_end && p.lse != nullptr)
+      p.lse[((int64_t)b * p.H + h) * p.nq + row] = (a.m_run + __builtin_log2f(l_tot)) * kLn2;
+  } else {
+#pragma unroll
+    for (int dm = 0; dm < D / 32; ++dm) a.o[dm] = f32x16{};
+    barrier();
+    // O = O alpha(j) + V^T P^T(j)
+    auto pv = [&](int j) {
+      if (!active) return;
+      const u32x4* src = pex + (j & 1) * kHalfP<D> + pair * kKG * 64 + a.lane;
+#pragma unroll
+      for (int g = 0; g < kKG; ++g) a.pf[g] = src[g * 64];
+      a.alpha = alf[(j & 1) * kHalfRows + pair * 32 + a.n];
+      a.rescale();
+      a.template mfma_slot<false, true, false>(0, j & 1);
+    };
+    for (int j = 0; j < n; ++j) {
+      if (j + 2 < n) a.load_k(j + 2, j & 1);
+      a.load_v(j, j & 1);
+      if (j > 0) pv(j - 1);
+      wait_vmcnt<0>();
+      barrier();
+    }
+    const float inv = alf[2 * kHalfRows + pair * 32 + a.n];
+    pv(n - 1);
+    if (active && row < q_end) store_row<D>(p, a.o, inv, b, h, row, a.hh);
+  }
+  if (RING) ring_append(p, D);
+}
+
+template <int D, bool NEG, bool RING>
+__global__ __launch_bounds__(kFwdThreads) void chunk_attn_fwd_half_kernel(const Params p,
+                                                                          const ClassTable tab) {
+  __shared__ __attribute__((aligned(16))) char lds[kHalfLds<D>];
+  int cl, bh, t;
+  decode_block(p, tab, cl, bh, t);
+  fwd_half_item<D, NEG, RING>(p, cl, bh, t, lds);
+}
+
 template <int D, bool NEG>
-hipError_t launch_t(const Params& p, bool ring, int64_t n_items, const ItemLists* lists, int n_groups,
+hipError_t launch_t(const Params& p, bool ring, const FwdPlan& plan, const ItemLists* lists, int n_groups,
                     hipStream_t stream) {
-  if (ring)
-    hipLaunchKernelGGL((chunk_attn_fwd_kernel<D, NEG, true>), dim3((unsigned)n_items), dim3(kFwdThreads), 0, stream,
-                       p);
+  const dim3 grid((unsigned)p.n_items), block(kFwdThreads);
+  if (plan.half && ring)
+    hipLaunchKernelGGL((chunk_attn_fwd_half_kernel<D, NEG, true>), grid, block, 0, stream, p, plan.tab);
+  else if (plan.half)
+    hipLaunchKernelGGL((chunk_attn_fwd_half_kernel<D, NEG, false>), grid, block, 0, stream, p, plan.tab);
+  else if (ring)
+    hipLaunchKernelGGL((chunk_attn_fwd_kernel<D, NEG, true>), grid, block, 0, stream, p, plan.tab);
   else if (lists != nullptr)
-    hipLaunchKernelGGL((chunk_attn_fwd_list_kernel<D, NEG>), dim3((unsigned)n_groups), dim3(kFwdThreads), 0, stream,
-                       p, *lists);
+    hipLaunchKernelGGL((chunk_attn_fwd_list_kernel<D, NEG>), dim3((unsigned)n_groups), block, 0, stream, p, *lists);
   else
-    hipLaunchKernelGGL((chunk_attn_fwd_kernel<D, NEG, false>), dim3((unsigned)n_items), dim3(kFwdThreads), 0, stream,
-                       p);
+    hipLaunchKernelGGL((chunk_attn_fwd_kernel<D, NEG, false>), grid, block, 0, stream, p, plan.tab);
   return hipGetLastError();
 }
 
@@ -911,22 +1145,31 @@ hipError_t launch_chunk_attn_fwd(const FwdArgs& a, hipStream_t stream) {
   p.ring_chunk = (int32_t)a.chunk_len;
   const bool neg = p.c < 0.f;
   // a few uneven items per CU: per-CU item lists (the CU count of the current
-  // device; any failure to query it keeps plain dispatch)
+  // device; any failure to query it keeps plain dispatch of 256-row items)
   ItemLists lists;
   const ItemLists* use_lists = nullptr;
   int n_groups = 0;
-  int n_cu = 0;
-  if (!ring && g.n_items > 0 && g.n_items <= kListMaxItems && (n_cu = device_cu_count()) > 0) {
-    const ItemShape shape{(int64_t)p.B * p.H, p.n_local_chunks, p.tiles_full, p.tiles_last, p.chunk_len,
-                          p.q_chunk_offset, p.window, p.nkv, kBK};
+  const int n_cu = device_cu_count();
+  const int64_t bh = a.B * a.H;
+  const ItemShape shape{bh, p.n_local_chunks, p.tiles_full, p.tiles_last, p.chunk_len,
+                        p.q_chunk_offset, p.window, p.nkv, kBK};
+  // 128-row items where 256-row ones leave CUs idle
+  const FwdGrid gh = fwd_grid(a.B, a.H, a.nq, L, kHalfRows);
+  FwdPlan plan;
+  fwd_plan(shape, gh.tiles_full, gh.tiles_last, (int)a.d, n_cu, &plan);
+  if (plan.half) {
+    p.tiles_full = (int32_t)gh.tiles_full;
+    p.tiles_last = (int32_t)gh.tiles_last;
+    p.n_items = (int32_t)gh.n_items;
+  } else if (!ring && g.n_items > 0 && g.n_items <= kListMaxItems && n_cu > 0) {
     static PlanCache plans;
     if (plans.plan(shape, (int)g.n_items, n_cu, &lists, &n_groups)) use_lists = &lists;
   }
   if (a.d == 128)
-    return neg ? launch_t<128, true>(p, ring, g.n_items, use_lists, n_groups, stream)
-               : launch_t<128, false>(p, ring, g.n_items, use_lists, n_groups, stream);
-  return neg ? launch_t<64, true>(p, ring, g.n_items, use_lists, n_groups, stream)
-             : launch_t<64, false>(p, ring, g.n_items, use_lists, n_groups, stream);
+    return neg ? launch_t<128, true>(p, ring, plan, use_lists, n_groups, stream)
+               : launch_t<128, false>(p, ring, plan, use_lists, n_groups, stream);
+  return neg ? launch_t<64, true>(p, ring, plan, use_lists, n_groups, stream)
+             : launch_t<64, false>(p, ring, plan, use_lists, n_groups, stream);
 }
 
 }  // namespace fastvr

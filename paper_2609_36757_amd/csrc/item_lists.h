@@ -45,14 +45,19 @@ inline int64_t item_chunk(const ItemShape& s, int64_t vi) {
   return vi < n_last ? s.n_local_chunks - 1 : s.n_local_chunks - 2 - (vi - n_last) / (s.bh * s.tiles_full);
 }
 
-// Work of item vi in key tiles, plus a fixed cost for its prologue and epilogue.
-inline int64_t item_cost(const ItemShape& s, int64_t vi) {
-  const int64_t cg = s.q_chunk_offset + item_chunk(s, vi);
+// Key tiles that an item of local query chunk c walks.
+inline int64_t chunk_key_tiles(const ItemShape& s, int64_t c) {
+  const int64_t cg = s.q_chunk_offset + c;
   const int64_t L = s.chunk_len;
   const int64_t lo = (s.window >= 0 && cg > s.window) ? (cg - s.window) * L : 0;
   const int64_t hi = (L < s.nkv - cg * L) ? (cg + 1) * L : s.nkv;
+  return (hi - lo + s.key_tile - 1) / s.key_tile;
+}
+
+// Work of item vi in key tiles, plus a fixed cost for its prologue and epilogue.
+inline int64_t item_cost(const ItemShape& s, int64_t vi) {
   constexpr int64_t kItemOverhead = 2;
-  return (hi - lo + s.key_tile - 1) / s.key_tile + kItemOverhead;
+  return chunk_key_tiles(s, item_chunk(s, vi)) + kItemOverhead;
 }
 
 // Minimum load over n bins (segment tree): the leftmost bin whose load is at

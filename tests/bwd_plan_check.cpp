@@ -46,21 +46,21 @@ static BwdShape make(int64_t bh, int64_t nq, int64_t nkv, int64_t L, int64_t off
 static void check(const BwdShape& s, int n_cu) {
   BwdPlan p;
   const int64_t n = bwd_plan(s, n_cu, &p);
-  CHECK(p.n_classes >= 1 && p.n_classes <= kBwdMaxClasses && p.first[0] == 0 && p.first[p.n_classes] == n);
+  CHECK(p.tab.n >= 1 && p.tab.n <= kMaxClasses && p.tab.first[0] == 0 && p.tab.first[p.tab.n] == n);
   CHECK((p.q_split == 1 || p.q_split == 2) && (p.kv_split == 1 || p.kv_split == 2));
   std::set<std::tuple<int, int64_t, int64_t, int64_t, int64_t>> seen;
   int64_t prev = INT64_MAX;
-  for (int k = 0; k < p.n_classes; ++k) {
-    const bool kv = p.is_kv[k] != 0;
+  for (int k = 0; k < p.tab.n; ++k) {
+    const bool kv = p.tab.kind[k] != 0;
     const int64_t split = kv ? p.kv_split : p.q_split, last = (kv ? s.n_kchunks : s.n_qchunks) - 1;
-    const int64_t blocks = kv ? (p.c0[k] == last ? s.kblocks_last : s.kblocks_full)
-                              : (p.c0[k] == last ? s.tiles_last : s.tiles_full);
+    const int64_t blocks = kv ? (p.tab.c0[k] == last ? s.kblocks_last : s.kblocks_full)
+                              : (p.tab.c0[k] == last ? s.tiles_last : s.tiles_full);
     int64_t longest = 0;
-    for (int64_t u = p.first[k]; u < p.first[k + 1]; ++u) {
-      int64_t r = u - p.first[k];
+    for (int64_t u = p.tab.first[k]; u < p.tab.first[k + 1]; ++u) {
+      int64_t r = u - p.tab.first[k];
       const int64_t per_bh = blocks * split, per_c = per_bh * s.bh;
-      const int64_t c = p.c0[k] + r / per_c;
-      CHECK(r / per_c < p.nc[k]);
+      const int64_t c = p.tab.c0[k] + r / per_c;
+      CHECK(r / per_c < p.tab.nc[k]);
       r %= per_c;
       const int64_t bh = r / per_bh, t = r % per_bh / split, half = r % split;
       CHECK(c <= last && bh < s.bh && half < split);
@@ -101,16 +101,16 @@ int main() {
   }
   // the grouped schedule against CU-by-CU simulation
   for (int i = 0; i < 200; ++i, ++cases) {
-    BwdClass cls[kBwdMaxClasses];
-    const int n = (int)pick(1, kBwdMaxClasses), cu = (int)pick(1, 256);
+    WorkClass cls[kMaxClasses];
+    const int n = (int)pick(1, kMaxClasses), cu = (int)pick(1, 256);
     std::vector<int64_t> load(cu, 0);
     int64_t cost = pick(50, 400);
     for (int k = 0; k < n; ++k) {
-      cls[k] = BwdClass{cost, pick(1, 300), 0, 1, 0};
+      cls[k] = WorkClass{cost, pick(1, 300), 0, 1, 0};
       cost -= std::min(cost - 1, pick(0, 12));
       for (int64_t u = 0; u < cls[k].units; ++u) *std::min_element(load.begin(), load.end()) += cls[k].cost;
     }
-    CHECK(bwd_makespan(cls, n, cu) == *std::max_element(load.begin(), load.end()));
+    CHECK(class_makespan(cls, n, cu) == *std::max_element(load.begin(), load.end()));
   }
   std::printf("%d cases ok\n", cases);
   return 0;

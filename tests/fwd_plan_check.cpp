@@ -1,0 +1,69 @@
+// CPU check of the forward's work plan (csrc/fwd_plan.h): over seeded shapes every
+// (chunk, batch * head, tile) comes from exactly one item index with either item
+// height, and the heights chosen for a few shapes.
+#include "fwd_plan.h"
+
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+#include <set>
+#include <tuple>
+
+using namespace fastvr;
+
+#define CHECK(x)                                         \
+  do {                                                   \
+    if (!(x)) {                                          \
+      std::printf("line %d: %s failed\n", __LINE__, #x); \
+      std::exit(1);                                      \
+    }                                                    \
+  } while (0)
+
+static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+static bool check(int64_t bh, int64_t nq, int64_t nkv, int64_t L, int64_t off, int64_t W, int d, int n_cu = 256) {
+  if (L > nkv) L = nkv;
+  const int64_t nc = cdiv(nq, L), last = nq - (nc - 1) * L;
+  auto tiles = [&](int64_t rows, int64_t& full, int64_t& tail) {
+    tail = cdiv(last, rows);
+    full = nc > 1 ? cdiv(L, rows) : tail;
+  };
+  ItemShape s{bh, nc, 0, 0, L, off, W, nkv, 96};
+  int64_t hf, hl;
+  tiles(256, s.tiles_full, s.tiles_last);
+  tiles(128, hf, hl);
+  FwdPlan p;
+  fwd_plan(s, hf, hl, d, n_cu, &p);
+  if (!p.half) hf = s.tiles_full, hl = s.tiles_last;
+  std::set<std::tuple<int64_t, int64_t, int64_t>> seen;
+  for (int k = 0; k < p.tab.n; ++k)
+    for (int64_t u = 0; u < p.tab.first[k + 1] - p.tab.first[k]; ++u) {
+      const int64_t t = p.tab.c0[k] == nc - 1 ? hl : hf, c = p.tab.c0[k] + u / (bh * t);
+      CHECK(c < p.tab.c0[k] + p.tab.nc[k] && c < nc);
+      CHECK(seen.insert({c, u % (bh * t) / t, u % t}).second);
+    }
+  CHECK((int64_t)seen.size() == bh * (hl + hf * (nc - 1)));
+  return p.half;
+}
+
+int main() {
+  std::mt19937_64 rng(11);
+  auto pick = [&](int64_t lo, int64_t hi) { return lo + (int64_t)(rng() % (uint64_t)(hi - lo + 1)); };
+  int n = 0, halves = 0;
+  for (; n < 400; ++n) {
+    const int64_t nkv = pick(1, 4000), L = pick(1, 900), off = std::min<int64_t>(pick(0, 3), (nkv - 1) / std::min(L, nkv));
+    halves += check(pick(1, 24), pick(1, nkv - off * std::min(L, nkv)), nkv, L, L > nkv ? 0 : off, pick(-1, 4),
+                    n % 2 ? 64 : 128, n % 3 ? 256 : (int)pick(1, 256));
+  }
+  CHECK(halves > 40 && halves < 360);
+  // 8 and 128 items of 256 rows leave CUs idle; 156 would need two waves of 128-row
+  // items; 768 fill the chip; the shapes of tests/test_gpu_half_items.py
+  CHECK(check(2, 1024, 1024, 256, 0, -1, 64) && check(4, 8192, 8192, 8192, 0, -1, 128));
+  CHECK(!check(12, 3120, 12480, 3120, 3, -1, 128) && !check(12, 16320, 65280, 16320, 3, -1, 128));
+  for (int d = 64; d <= 128; d += 64) {
+    CHECK(check(2, 900, 900, 259, 0, -1, d) && check(2, 259, 518, 259, 1, 1, d));
+    CHECK(!check(256, 900, 900, 259, 0, -1, d) && !check(512, 259, 518, 259, 1, 1, d));
+  }
+  std::printf("%d cases ok\n", n);
+  return 0;
+}

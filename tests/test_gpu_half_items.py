@@ -1,0 +1,62 @@
+"""128-row against 256-row items of the forward, bit for bit: a small call runs
+128-row items, the same tensors repeated as a large batch 256-row ones
+(tests/fwd_plan_check.cpp checks both plans).  Odd chunk lengths leave ragged
+tiles in both heights and a ragged last key tile; interval lengths are even and
+odd numbers of key tiles.  One case of each is also held against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2609_36757_amd import fastvr
+from paper_2609_36757_amd.workloads import make_qkv
+
+from parity import compare, run_oracle, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    fastvr.load()
+    return torch.device("cuda:0")
+
+
+@pytest.mark.parametrize("d,scale,L,N,off,W,reps", [
+    (64, 0.125, 259, 900, 0, -1, 128), (128, 1 / np.sqrt(128), 259, 900, 0, -1, 128),
+    (64, -0.2, 259, 900, 0, -1, 128), (128, -0.08, 259, 900, 0, -1, 128),
+    (128, 1 / np.sqrt(128), 259, 259, 1, 1, 256), (64, 0.125, 259, 259, 1, 1, 256)])
+def test_half_items_equal_full_items(dev, d, scale, L, N, off, W, reps):
+    H, nkv = 2, off * L + N
+    print(f"\n[gpu case] half items: H={H} d={d} N={N} Nkv={nkv} L={L} off={off} W={W} scale={scale:.3f}", flush=True)
+    q, k, v = make_qkv(1, N, nkv, H, d, seed=600 + d + off)
+    kw = dict(chunk_len=L, q_chunk_offset=off, window_chunks=W, scale=scale)
+    small = [t.to(dev) for t in (q, k, v)]
+    o, lse = fastvr.chunk_attn(*small, **kw)
+    big_o, big_l = fastvr.chunk_attn(*(t.expand(reps, *t.shape[1:]).contiguous() for t in small), **kw)
+    ob = torch.empty_like(o, dtype=torch.bfloat16)
+    fastvr.chunk_attn(*small, out=ob, return_lse=False, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(o.expand_as(big_o), big_o) and torch.equal(lse.expand_as(big_l), big_l)
+    assert torch.equal(ob, o.to(torch.bfloat16))
+    o_ref, l_ref = run_oracle(q, k, v, L, off, W, scale)
+    compare(to_np(o), to_np(lse), o_ref, l_ref, label=f"half items d={d} scale={scale:.3f} off={off}")
+
+
+@pytest.mark.parametrize("d,L", [(128, 260), (64, 264)])
+def test_half_items_ring_step(dev, d, L):
+    """The ring step with 128-row items, whose key tiles straddle two slots, against
+    the same step over a large batch (256-row items): outputs and ring."""
+    H, W, c, n_new, reps = 2, 1, 3, 200, 256
+    print(f"\n[gpu case] half items ring: H={H} d={d} L={L} W={W} c={c} n_new={n_new}", flush=True)
+    q, k, v = (t.to(dev) for t in make_qkv(1, n_new, n_new, H, d, seed=640 + d))
+    _, rk, rv = (t.to(dev) for t in make_qkv(1, 1, (W + 1) * L, H, d, seed=641 + d))
+    outs = []
+    for r in (1, reps):
+        args = [t.expand(r, *t.shape[1:]).contiguous() for t in (q, k, v, rk, rv)]
+        o, lse = fastvr.chunk_attn_ring_step(*args, chunk_len=L, chunk_index=c, window_chunks=W)
+        outs.append((o, lse, args[3], args[4]))
+    torch.cuda.synchronize()
+    for a, b in zip(*outs):
+        assert torch.equal(a.expand_as(b), b)
