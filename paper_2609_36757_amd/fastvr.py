@@ -6,6 +6,7 @@ If the library is missing, every call raises; there is no fallback."""
 from __future__ import annotations
 
 import ctypes
+import functools
 import math
 import os
 
@@ -161,10 +162,16 @@ def tile_blend_update_raw(v_tiles, z_lq, z_hat, sigma, B, T, Hg, Wg, C, tile, ov
 # torch-facing wrappers
 # ---------------------------------------------------------------------------
 
+# The checks and allocations below are on the path of calls whose kernels take
+# 5 to 20 us.  Measured on the host: torch.cuda.current_stream() 2.8 us against
+# 0.1 us for its raw handle; torch.empty(..., device=...) 1.8 us against 1.3 to
+# 1.6 us for empty_like / new_empty.
+
 def _stream_handle(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    from torch import _C
+    return _C._cuda_getCurrentRawStream(_C._cuda_getDevice())  # current stream of the current device
 
 
 def _bnhd_strides(t, name):
@@ -186,35 +193,40 @@ def chunk_attn(q, k, v, *, chunk_len: int, q_chunk_offset: int = 0, window_chunk
     [B, H, Nq] or None); o is fp32 unless ``out`` is a bfloat16 tensor, which
     receives O rounded to bf16."""
     import torch
+    bf16, fp32 = torch.bfloat16, torch.float32
     for name, t in (("q", q), ("k", k), ("v", v)):
-        if t.dtype != torch.bfloat16 or not t.is_cuda:
+        if t.dtype != bf16 or not t.is_cuda:
             raise ValueError(f"{name} must be a bfloat16 GPU tensor")
-    B, Nq, H, d = q.shape
-    Nkv = k.shape[1]
-    if k.shape != (B, Nkv, H, d) or v.shape != k.shape:
-        raise ValueError(f"shape mismatch: q {tuple(q.shape)} k {tuple(k.shape)} v {tuple(v.shape)}")
+    shape, kv_shape = q.shape, k.shape
+    B, Nq, H, d = shape
+    Nkv = kv_shape[1]
+    if kv_shape != (B, Nkv, H, d) or v.shape != kv_shape:
+        raise ValueError(f"shape mismatch: q {tuple(shape)} k {tuple(kv_shape)} v {tuple(v.shape)}")
     if scale is None:
         scale = 1.0 / math.sqrt(d)
     if out is None:
-        out = torch.empty((B, Nq, H, d), dtype=torch.float32, device=q.device)
-    if out.dtype not in (torch.float32, torch.bfloat16) or tuple(out.shape) != (B, Nq, H, d):
-        raise ValueError("out must be float32 or bfloat16 [B, Nq, H, d]")
-    o_bf16 = 1 if out.dtype == torch.bfloat16 else 0
-    if return_lse and lse is None:
-        lse = torch.empty((B, H, Nq), dtype=torch.float32, device=q.device)
-    if lse is not None and (lse.dtype != torch.float32 or tuple(lse.shape) != (B, H, Nq)
-                            or not lse.is_contiguous()):
-        raise ValueError("lse must be a contiguous float32 [B, H, Nq] tensor")
+        out = q.new_empty(shape, dtype=fp32)
+        o_bf16 = 0
+    else:
+        o_bf16 = 1 if out.dtype == bf16 else 0
+        if not o_bf16 and out.dtype != fp32 or out.shape != shape:
+            raise ValueError("out must be float32 or bfloat16 [B, Nq, H, d]")
+    if lse is not None:
+        if lse.dtype != fp32 or lse.shape != (B, H, Nq) or not lse.is_contiguous():
+            raise ValueError("lse must be a contiguous float32 [B, H, Nq] tensor")
+    elif return_lse:
+        lse = q.new_empty((B, H, Nq), dtype=fp32)
     lse_ptr = lse.data_ptr() if lse is not None else None
     st = _stream_handle(stream)
-    if not o_bf16 and all(t.is_contiguous() for t in (q, k, v, out)):
-        status = fwd_raw(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse_ptr, B, H, Nq, Nkv, d,
-                         chunk_len, q_chunk_offset, window_chunks, scale, st)
+    if not o_bf16 and q.is_contiguous() and k.is_contiguous() and v.is_contiguous() and out.is_contiguous():
+        status = load().fastvr_chunk_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse_ptr, B, H,
+                                              Nq, Nkv, d, chunk_len, q_chunk_offset, window_chunks, scale, st)
     else:
         qs, ks, vs, os_ = (_bnhd_strides(t, n) for t, n in ((q, "q"), (k, "k"), (v, "v"), (out, "out")))
         status = fwd_ex_raw(q.data_ptr(), *qs, k.data_ptr(), *ks, v.data_ptr(), *vs, out.data_ptr(), *os_, o_bf16,
                             lse_ptr, B, H, Nq, Nkv, d, chunk_len, q_chunk_offset, window_chunks, scale, st)
-    _check(status)
+    if status:
+        _check(status)
     return out, lse
 
 
@@ -257,11 +269,11 @@ def chunk_attn_ring_step(q_new, k_new, v_new, k_ring, v_ring, *, chunk_len: int,
     if scale is None:
         scale = 1.0 / math.sqrt(d)
     if out is None:
-        out = torch.empty((B, n_new, H, d), dtype=torch.float32, device=q_new.device)
+        out = q_new.new_empty((B, n_new, H, d), dtype=torch.float32)
     if out.dtype != torch.float32 or tuple(out.shape) != (B, n_new, H, d) or not out.is_contiguous():
         raise ValueError("out must be a contiguous float32 [B, n_new, H, d] tensor")
     if return_lse and lse is None:
-        lse = torch.empty((B, H, n_new), dtype=torch.float32, device=q_new.device)
+        lse = q_new.new_empty((B, H, n_new), dtype=torch.float32)
     if lse is not None and (lse.dtype != torch.float32 or tuple(lse.shape) != (B, H, n_new)
                             or not lse.is_contiguous()):
         raise ValueError("lse must be a contiguous float32 [B, H, n_new] tensor")
@@ -289,7 +301,7 @@ def chunk_attn_bwd(q, k, v, o, lse, dout, *, chunk_len: int, q_chunk_offset: int
         raise ValueError(f"shape mismatch: q {tuple(q.shape)} k {tuple(k.shape)} v {tuple(v.shape)} "
                          f"dout {tuple(dout.shape)}")
     for name, t, shape in (("o", o, (B, Nq, H, d)), ("lse", lse, (B, H, Nq))):
-        if t.dtype != torch.float32 or tuple(t.shape) != shape or not t.is_contiguous():
+        if t.dtype != torch.float32 or t.shape != shape or not t.is_contiguous():
             raise ValueError(f"{name} must be a contiguous float32 {list(shape)} tensor")
     if scale is None:
         scale = 1.0 / math.sqrt(d)
@@ -297,8 +309,8 @@ def chunk_attn_bwd(q, k, v, o, lse, dout, *, chunk_len: int, q_chunk_offset: int
     for name, t, shape in (("dq", dq, (B, Nq, H, d)), ("dk", dk, (B, Nkv, H, d)), ("dv", dv, (B, Nkv, H, d)),
                            ("row_stats", row_stats, (B, H, 2, Nq))):
         if t is None:
-            t = torch.empty(shape, dtype=torch.float32, device=q.device)
-        if t.dtype != torch.float32 or tuple(t.shape) != shape or not t.is_contiguous():
+            t = q.new_empty(shape, dtype=torch.float32)
+        elif t.dtype != torch.float32 or t.shape != shape or not t.is_contiguous():
             raise ValueError(f"{name} must be a contiguous float32 {list(shape)} tensor")
         outs.append(t)
     dq, dk, dv, row_stats = outs
@@ -326,7 +338,7 @@ def chunk_attn_bwd_noalloc(q, k, v, o, lse, dout, dq, dk, dv, *, chunk_len: int,
                          f"dout {tuple(dout.shape)}")
     for name, t, shape in (("o", o, (B, Nq, H, d)), ("lse", lse, (B, H, Nq)), ("dq", dq, (B, Nq, H, d)),
                            ("dk", dk, (B, Nkv, H, d)), ("dv", dv, (B, Nkv, H, d))):
-        if t.dtype != torch.float32 or tuple(t.shape) != shape or not t.is_contiguous():
+        if t.dtype != torch.float32 or t.shape != shape or not t.is_contiguous():
             raise ValueError(f"{name} must be a contiguous float32 {list(shape)} tensor")
     if scale is None:
         scale = 1.0 / math.sqrt(d)
@@ -353,17 +365,21 @@ def one_step_update(z_lq, v, sigma: float, *, out=None, out_dtype=None, stream=N
     if out_dtype not in (torch.float32, torch.bfloat16):
         raise ValueError("out_dtype must be float32 or bfloat16")
     if out is None:
-        out = torch.empty(z_lq.shape, dtype=out_dtype, device=z_lq.device)
-    if out.dtype != out_dtype or out.shape != z_lq.shape or not out.is_contiguous():
+        out = z_lq.new_empty(z_lq.shape, dtype=out_dtype)
+    elif out.dtype != out_dtype or out.shape != z_lq.shape or not out.is_contiguous():
         raise ValueError("out must be a contiguous tensor of z_lq's shape and dtype out_dtype")
     _check(one_step_raw(z_lq.data_ptr(), v.data_ptr(), out.data_ptr(), z_lq.numel(), sigma,
                         1 if out_dtype == torch.bfloat16 else 0, _stream_handle(stream)))
     return out
 
 
+# a pure function of three integers; typed, so that what tile_axis refuses stays refused
+_axis = functools.lru_cache(maxsize=64, typed=True)(tile_axis)
+
+
 def _tile_shape(B, T, Hg, Wg, C, tile, overlap):
-    ny, Ly = tile_axis(Hg, tile, overlap)
-    nx, Lx = tile_axis(Wg, tile, overlap)
+    ny, Ly = _axis(Hg, tile, overlap)
+    nx, Lx = _axis(Wg, tile, overlap)
     return (B, ny * nx, T, Ly, Lx, C)
 
 
@@ -376,8 +392,8 @@ def tile_gather(x, *, tile: int = 64, overlap: int = 16, out=None, stream=None):
     B, T, Hg, Wg, C = x.shape
     shape = _tile_shape(B, T, Hg, Wg, C, tile, overlap)
     if out is None:
-        out = torch.empty(shape, dtype=torch.bfloat16, device=x.device)
-    if out.dtype != torch.bfloat16 or tuple(out.shape) != shape or not out.is_contiguous():
+        out = x.new_empty(shape)
+    elif out.dtype != torch.bfloat16 or tuple(out.shape) != shape or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous bfloat16 tensor of shape {shape}")
     _check(tile_gather_raw(x.data_ptr(), out.data_ptr(), B, T, Hg, Wg, C, tile, overlap, _stream_handle(stream)))
     return out
@@ -396,8 +412,8 @@ def tile_blend(tiles, Hg: int, Wg: int, *, tile: int = 64, overlap: int = 16, z_
         raise ValueError("tiles do not match the grid, tile and overlap")
     shape = (B, T, Hg, Wg, C)
     if out is None:
-        out = torch.empty(shape, dtype=torch.float32, device=tiles.device)
-    if out.dtype != torch.float32 or tuple(out.shape) != shape or not out.is_contiguous():
+        out = tiles.new_empty(shape)
+    elif out.dtype != torch.float32 or tuple(out.shape) != shape or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous float32 tensor of shape {shape}")
     st = _stream_handle(stream)
     if z_lq is None:
