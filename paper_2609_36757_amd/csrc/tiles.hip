@@ -34,39 +34,12 @@ struct Axis {
   int n, L, span;  // tiles, tile length, size - L
 };
 
-__device__ __forceinline__ int origin(const Axis& a, int k) {
-  return a.n == 1 ? 0 : (int)(((int64_t)k * a.span + (a.n - 1) / 2) / (a.n - 1));
-}
-
 __device__ __forceinline__ int axis_weight(int i, int L, int R) {
   const int m = (i + 1 < L - i) ? i + 1 : L - i;
   return m < R ? m : R;
 }
 
-// One tile row (b, tile, t, iy) per loop step of a workgroup; 16-byte units.
-__global__ __launch_bounds__(kThreads) void tile_gather_kernel(const u32x4* __restrict__ x, u32x4* __restrict__ tiles,
-                                                               int T, int Hg, int Wg, int C16, Axis ay, Axis ax,
-                                                               int64_t n_rows) {
-  const int64_t row_units = (int64_t)ax.L * C16;
-  for (int64_t r = blockIdx.x; r < n_rows; r += gridDim.x) {
-    // r = ((b * nt + tile) * T + t) * Ly + iy  (wave-uniform)
-    int64_t q = r;
-    const int iy = (int)(q % ay.L);
-    q /= ay.L;
-    const int t = (int)(q % T);
-    q /= T;
-    const int nt = ay.n * ax.n;
-    const int tile = (int)(q % nt);
-    const int64_t b = q / nt;
-    const int ty = tile / ax.n, tx = tile - ty * ax.n;
-    const int y = origin(ay, ty) + iy, x0 = origin(ax, tx);
-    const u32x4* src = x + (((b * T + t) * Hg + y) * (int64_t)Wg + x0) * C16;
-    u32x4* dst = tiles + r * row_units;
-    for (int64_t u = threadIdx.x; u < row_units; u += kThreads) __builtin_nontemporal_store(src[u], dst + u);
-  }
-}
-
-// Index arithmetic of the blend in type I: uint32_t when every numerator below
+// Index arithmetic in type I: uint32_t when every numerator below
 // fits (the usual case), uint64_t otherwise.
 template <typename I>
 __device__ __forceinline__ int origin_t(const Axis& a, int k) {
@@ -91,6 +64,59 @@ __device__ __forceinline__ int first_end_gt(const Axis& a, int p) {
   return m < 0 ? 0 : last_start_le<I>(a, m) + 1;
 }
 
+// Gather.  Work item = (field row r = (b * T + t) * Hg + y, segment of kThreads *
+// U consecutive 16-byte units of it).  A thread reads its U units (kThreads
+// apart) once and writes them to every tile that holds them; the tiles covering
+// the row (along y) and the segment's positions (along x) are two index ranges
+// found in closed form.  A tile row is a contiguous run of the field row, so unit
+// u of the field row is unit u - ox * C16 of the tile row at origin ox.
+// Bound by the HBM writes: each field unit is read once from memory, where one
+// workgroup per tile row read every tile's share of it again.  6 tiles of 8 x 64 x
+// 64 x 1536 (604 MB written, 200 MB read) 175.6 -> 115.4 us, 7.0 TB/s; 2 x 12
+// tiles of 32 x 32 rows, 768 channels 82.8 -> 63.1 us; a single tile (a plain
+// copy) 18.5 -> 17.8 us.  Three units a thread: two were 5% slower on the single
+// tile, four 1 to 2% on many small tiles; field loads past the caches cost 20%.
+constexpr int kGatherUnits = 3;
+template <typename I>
+__global__ __launch_bounds__(kThreads) void tile_gather_kernel(const u32x4* __restrict__ x, u32x4* __restrict__ tiles,
+                                                               int T, int Hg, int Wg, int C16, Axis ay, Axis ax,
+                                                               int64_t n_rows) {
+  constexpr int U = kGatherUnits;
+  const int row_units = Wg * C16;
+  const int tile_units = ax.L * C16;  // of one tile row
+  const int nt = ay.n * ax.n;
+  const int64_t tile_rows = (int64_t)T * ay.L;
+  const int u_begin = blockIdx.x * (kThreads * U);
+  const int u_end = min(u_begin + kThreads * U, row_units);
+  const int tx_lo = first_end_gt<I>(ax, u_begin / C16), tx_hi = last_start_le<I>(ax, (u_end - 1) / C16);
+  for (int64_t r = blockIdx.y; r < n_rows; r += gridDim.y) {
+    u32x4 val[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int u = u_begin + k * kThreads + (int)threadIdx.x;
+      if (u < u_end) val[k] = x[r * row_units + u];
+    }
+    const I rr = (I)r;
+    const int y = (int)(rr % (I)Hg);
+    const I bt = rr / (I)Hg;
+    const int t = (int)(bt % (I)T);
+    const int64_t b = (int64_t)(bt / (I)T);
+    const int ty_hi = last_start_le<I>(ay, y);
+    for (int ty = first_end_gt<I>(ay, y); ty <= ty_hi; ++ty) {
+      const int64_t row0 = ((b * nt + ty * ax.n) * T + t) * ay.L + (y - origin_t<I>(ay, ty));  // tile row for tx = 0
+      for (int tx = tx_lo; tx <= tx_hi; ++tx) {
+        const int u0 = origin_t<I>(ax, tx) * C16;
+        u32x4* dst = tiles + (row0 + (int64_t)tx * tile_rows) * tile_units;
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+          const int u = u_begin + k * kThreads + (int)threadIdx.x, v = u - u0;
+          if (u < u_end && v >= 0 && v < tile_units) __builtin_nontemporal_store(val[k], dst + v);
+        }
+      }
+    }
+  }
+}
+
 // Work item = (output row r = (b * T + t) * Hg + y, segment of kThreads * U
 // consecutive units of that row); a unit is 4 channels of one position (16 bytes
 // of fp32).  The tiles covering the row (along y) and the segment's positions
@@ -98,16 +124,11 @@ __device__ __forceinline__ int first_end_gt(const Axis& a, int p) {
 // then forms its U units (kThreads apart), issuing the loads of all U units
 // from one tile before using any.  With Z (fused Eq. 9) the output is
 // z - sigma * blend, z bf16.
-#ifndef FASTVR_BLEND_UNITS
-#define FASTVR_BLEND_UNITS 4
-#endif
-constexpr int kBlendUnits = FASTVR_BLEND_UNITS;
-template <bool Z, typename I>
+template <bool Z, typename I, int U, bool STREAM>
 __global__ __launch_bounds__(kThreads) void tile_blend_kernel(const float* __restrict__ tiles,
                                                               const uint16_t* __restrict__ z, float* __restrict__ out,
                                                               float neg_sigma, int T, int Hg, int Wg, int C, Axis ay,
                                                               Axis ax, int R, int64_t n_rows) {
-  constexpr int U = kBlendUnits;
   const int C4 = C / 4;
   const int row_units = Wg * C4;
   const int nt = ay.n * ax.n;
@@ -154,8 +175,8 @@ __global__ __launch_bounds__(kThreads) void tile_blend_kernel(const float* __res
           w[k] = 0.f;
           if (ok[k] && ix >= 0 && ix < ax.L) {
             w[k] = (float)(wy * axis_weight(ix, ax.L, R));
-            // each tile element is read exactly once: stream it past the caches
-            val[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(trow + (int64_t)ix * C + 4 * c4[k]));
+            const f32x4* src = reinterpret_cast<const f32x4*>(trow + (int64_t)ix * C + 4 * c4[k]);
+            val[k] = STREAM ? __builtin_nontemporal_load(src) : *src;
           }
         }
 #pragma unroll
@@ -191,17 +212,33 @@ Axis make_axis(int64_t size, int64_t tile, int64_t overlap) {
   return Axis{(int)t.n, (int)t.len, (int)(size - t.len)};
 }
 
-unsigned grid_for(int64_t rows) { return (unsigned)(rows < 8192 ? (rows < 1 ? 1 : rows) : 8192); }
+// 32-bit index arithmetic when the row index and every origin numerator (below
+// n * size along each axis) stay below 2^32.
+bool narrow_index(int64_t rows, const Axis& ay, const Axis& ax, int64_t Hg, int64_t Wg) {
+  const int64_t lim = int64_t(1) << 32;
+  return rows < lim && (int64_t)ay.n * Hg < lim && (int64_t)ax.n * Wg < lim;
+}
+
+dim3 row_grid(int64_t row_units, int64_t rows, int units) {
+  return dim3((unsigned)((row_units + kThreads * units - 1) / (kThreads * units)),
+              (unsigned)(rows < 65535 ? rows : 65535));
+}
 
 }  // namespace
 
 hipError_t launch_tile_gather(const void* x, void* tiles, int64_t B, int64_t T, int64_t Hg, int64_t Wg, int64_t C,
                               int64_t tile, int64_t overlap, hipStream_t stream) {
   const Axis ay = make_axis(Hg, tile, overlap), ax = make_axis(Wg, tile, overlap);
-  const int64_t rows = B * ay.n * ax.n * T * ay.L;
-  hipLaunchKernelGGL(tile_gather_kernel, dim3(grid_for(rows)), dim3(kThreads), 0, stream,
-                     static_cast<const u32x4*>(x), static_cast<u32x4*>(tiles), (int)T, (int)Hg, (int)Wg, (int)(C / 8),
-                     ay, ax, rows);
+  const int64_t rows = B * T * Hg;
+  const dim3 grid = row_grid(Wg * (C / 8), rows, kGatherUnits);
+  const u32x4* xp = static_cast<const u32x4*>(x);
+  u32x4* tp = static_cast<u32x4*>(tiles);
+  if (narrow_index(rows, ay, ax, Hg, Wg))
+    hipLaunchKernelGGL(tile_gather_kernel<uint32_t>, grid, dim3(kThreads), 0, stream, xp, tp, (int)T, (int)Hg, (int)Wg,
+                       (int)(C / 8), ay, ax, rows);
+  else
+    hipLaunchKernelGGL(tile_gather_kernel<uint64_t>, grid, dim3(kThreads), 0, stream, xp, tp, (int)T, (int)Hg, (int)Wg,
+                       (int)(C / 8), ay, ax, rows);
   return hipGetLastError();
 }
 
@@ -211,24 +248,33 @@ hipError_t launch_tile_blend(const float* tiles, const void* z_lq, float* out, f
   const int64_t rows = B * T * Hg;
   const int R = overlap > 1 ? (int)overlap : 1;
   const int64_t row_units = Wg * (C / 4);
-  const dim3 grid((unsigned)((row_units + kThreads * kBlendUnits - 1) / (kThreads * kBlendUnits)),
-                  (unsigned)(rows < 65535 ? rows : 65535));
-  // 32-bit index arithmetic when the row index and every origin numerator
-  // (below n * size along each axis) stay below 2^32
-  const int64_t lim = int64_t(1) << 32;
-  const bool narrow = rows < lim && (int64_t)ay.n * Hg < lim && (int64_t)ax.n * Wg < lim;
+  const bool narrow = narrow_index(rows, ay, ax, Hg, Wg);
+  // Tiles that fit the 256 MB Infinity Cache are usually still there (the call
+  // that produced them ran just before) and are read through the caches, two
+  // units a thread for more waves: 6 tiles of 8 x 64 x 64 x 48 14.9 -> 11.3 us,
+  // 277 MB of tiles 73.5 -> 62.9 us.  Larger ones are each read exactly once and
+  // streamed past the caches, four units a thread: 1.2 GB 257 against 284 us,
+  // 470 MB 92 against 100 us.  The line is drawn between, at 1.25 times that cache.
+  const bool streamed = B * ay.n * ax.n * T * ay.L * ax.L * C * 4 > ((int64_t)320 << 20);
+  const dim3 grid = row_grid(row_units, rows, streamed ? 4 : 2);
   const uint16_t* zp = static_cast<const uint16_t*>(z_lq);
   const float ns = z_lq != nullptr ? -sigma : 0.f;
-#define FASTVR_BLEND_LAUNCH(ZV, IT)                                                                              \
-  hipLaunchKernelGGL((tile_blend_kernel<ZV, IT>), grid, dim3(kThreads), 0, stream, tiles, zp, out, ns, (int)T, \
+#define FASTVR_BLEND_LAUNCH(ZV, IT, UV, SV)                                                                             \
+  hipLaunchKernelGGL((tile_blend_kernel<ZV, IT, UV, SV>), grid, dim3(kThreads), 0, stream, tiles, zp, out, ns, (int)T, \
                      (int)Hg, (int)Wg, (int)C, ay, ax, R, rows)
+#define FASTVR_BLEND_INDEX(ZV, UV, SV)                      \
+  do {                                                      \
+    if (narrow) FASTVR_BLEND_LAUNCH(ZV, uint32_t, UV, SV);  \
+    else FASTVR_BLEND_LAUNCH(ZV, uint64_t, UV, SV);         \
+  } while (0)
   if (z_lq != nullptr) {
-    if (narrow) FASTVR_BLEND_LAUNCH(true, uint32_t);
-    else FASTVR_BLEND_LAUNCH(true, uint64_t);
+    if (streamed) FASTVR_BLEND_INDEX(true, 4, true);
+    else FASTVR_BLEND_INDEX(true, 2, false);
   } else {
-    if (narrow) FASTVR_BLEND_LAUNCH(false, uint32_t);
-    else FASTVR_BLEND_LAUNCH(false, uint64_t);
+    if (streamed) FASTVR_BLEND_INDEX(false, 4, true);
+    else FASTVR_BLEND_INDEX(false, 2, false);
   }
+#undef FASTVR_BLEND_INDEX
 #undef FASTVR_BLEND_LAUNCH
   return hipGetLastError();
 }

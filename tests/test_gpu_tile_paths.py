@@ -1,0 +1,51 @@
+"""The gather around the edges of its 768-unit segments and in grids of one tile,
+bit for bit against slicing; the blend of a tile tensor past the 320 MB line (read
+past the caches) bit for bit against the same field blended batch by batch (read
+through them)."""
+import pytest
+import torch
+
+import oracle
+from paper_2609_36757_amd import fastvr
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    fastvr.load()
+    return torch.device("cuda:0")
+
+
+# Hg, Wg, C, tile, overlap: one row is Wg * C / 8 units of 16 bytes
+@pytest.mark.parametrize("Hg,Wg,C,tile,overlap", [(5, 767, 8, 64, 16), (70, 768, 8, 64, 0), (5, 769, 8, 64, 16),
+                                                  (9, 11, 560, 64, 16), (33, 97, 64, 32, 31), (1, 1, 8, 1, 0)])
+def test_gather_equals_slices(dev, Hg, Wg, C, tile, overlap):
+    B, T = 2, 3
+    print(f"\n[gpu case] gather B={B} T={T} {Hg}x{Wg} C={C} tile={tile} overlap={overlap}", flush=True)
+    x = torch.randint(-30000, 30000, (B, T, Hg, Wg, C), dtype=torch.int16, device=dev).view(torch.bfloat16)
+    got = fastvr.tile_gather(x, tile=tile, overlap=overlap).view(torch.int16)
+    torch.cuda.synchronize()
+    oy, Ly = oracle.tile_axis(Hg, tile, overlap)
+    ox, Lx = oracle.tile_axis(Wg, tile, overlap)
+    for ty, y in enumerate(oy):
+        for tx, c in enumerate(ox):
+            assert torch.equal(got[:, ty * len(ox) + tx], x.view(torch.int16)[:, :, y:y + Ly, c:c + Lx])
+
+
+@pytest.mark.parametrize("update", [False, True])
+def test_streamed_blend_equals_cached(dev, update):
+    B, T, Hg, Wg, C = 6, 4, 70, 90, 256
+    print(f"\n[gpu case] blend B={B} T={T} {Hg}x{Wg} C={C} update={update}", flush=True)
+    ny, Ly = fastvr.tile_axis(Hg, 64, 16)
+    nx, Lx = fastvr.tile_axis(Wg, 64, 16)
+    tiles = torch.randn((B, ny * nx, T, Ly, Lx, C), device=dev)
+    assert tiles.numel() * 4 > 320 << 20 > tiles[0].numel() * 4
+    z = torch.randn((B, T, Hg, Wg, C), device=dev).to(torch.bfloat16) if update else None
+    whole = fastvr.tile_blend(tiles, Hg, Wg, z_lq=z, sigma=0.4)
+    for b in range(B):
+        one = fastvr.tile_blend(tiles[b:b + 1], Hg, Wg, z_lq=z[b:b + 1] if update else None, sigma=0.4)
+        torch.cuda.synchronize()
+        assert torch.equal(one[0], whole[b]), b
