@@ -906,6 +906,70 @@ constexpr int kHalfLds = 2 * 2 * kBK * D * 2 + 2 * kHalfP<D> * 16 + 3 * kHalfRow
 
 template <int D, bool NEG, bool RING>
 struct HalfAttn : Attn<D, NEG, RING> {
+  using Base = Attn<D, NEG, RING>;
+  // Where the tiles of a ring step have got to: the chunk of the last tile
+  // loaded, as the address its virtual row 0 would have (row r at base + r * st)
+  // and the virtual row after its last full row.  Tiles are loaded in order, so
+  // the chunk is looked up once per chunk instead of once per tile (3 x 1200 + 1100
+  // rows, 4 heads: 86.7 -> 81.9 us; 3 x 9000, 8 heads, d = 64: 1320 -> 1137 us).  Not
+  // done in the 256-row items: their roles branch on a vector register, so the
+  // compiler keeps the place in vector registers, which they do not have (2.79 ->
+  // 3.14 ms at 16320 rows), and a scalar wave index makes it spill the main loop.
+  struct RingPos {
+    const uint16_t* base;
+    int seg, end;
+  };
+  RingPos k_pos, v_pos;
+  template <bool IS_K>
+  __device__ __forceinline__ void ring_to(int seg) {
+    const typename Base::RingSeg sg = this->template ring_seg<IS_K>(seg);
+    RingPos& ps = IS_K ? k_pos : v_pos;
+    ps = RingPos{sg.base - (int64_t)sg.start * (IS_K ? this->k_st : this->v_st), seg, sg.start + this->ring_L};
+  }
+
+  template <bool IS_K>
+  __device__ __forceinline__ void load_tracked(int j, int stage) {
+    constexpr int kRowsPerInst = 64 / Base::kChunks;
+    const int t0 = __builtin_amdgcn_readfirstlane(this->lo + j * kBK);
+    const int w0 = __builtin_amdgcn_readfirstlane((this->wave % Base::kDmaWaves) * kRowsPerInst);
+    RingPos& ps = IS_K ? k_pos : v_pos;
+    if (t0 >= ps.end && ps.seg + 1 < this->n_seg) ring_to<IS_K>(ps.seg + 1);
+    const bool last = ps.seg + 1 >= this->n_seg;
+    if (last || t0 + kBK <= ps.end) {
+      // the whole tile lies in one chunk (all but one tile per chunk
+      // boundary): the plain tile DMA from that chunk
+      const int rows = (last ? ps.end - this->ring_L + this->n_last : ps.end) - t0;
+      const int valid = rows < 0 ? 0 : (rows > kBK ? kBK : rows);
+      if (IS_K)
+        this->dma_k(ps.base + (int64_t)t0 * this->k_st, valid, stage);
+      else
+        this->dma_v(ps.base + (int64_t)t0 * this->v_st, valid, stage);
+      return;
+    }
+    const typename Base::RingSeg s0 = this->template ring_seg<IS_K>(ps.seg), s1 = this->template ring_seg<IS_K>(ps.seg + 1);
+#pragma unroll
+    for (int i = 0; i < Base::kDmaPer; ++i) {
+      const int r0 = t0 + i * Base::kDmaWaves * kRowsPerInst + w0;
+      this->template dma_inst_ring<IS_K>(r0 >= s1.start ? s1 : s0, r0, stage, i);
+    }
+  }
+
+  __device__ __forceinline__ void ring_init() {
+    const int seg = this->ring_seg_of(this->lo);
+    ring_to<true>(seg);
+    ring_to<false>(seg);
+  }
+  // DMA of K (or V) tile j into LDS stage `stage`
+  template <bool IS_K>
+  __device__ __forceinline__ void load(int j, int stage) {
+    if (RING && this->ring_L >= kBK)
+      load_tracked<IS_K>(j, stage);
+    else if (IS_K)
+      this->load_k(j, stage);
+    else
+      this->load_v(j, stage);
+  }
+
   static constexpr int kN = D * kBK / 512;  // MFMAs of S or of P.V
 
   // sn = K Q^T of the tile in K stage kst (QK), with the softmax of the scores
@@ -962,14 +1026,15 @@ __device__ __forceinline__ void fwd_half_item(const Params& p, int cl, int bh, i
   int b, h, q_end, q0;
   item_rows<A, D, RING>(p, cl, bh, t, kHalfRows, a, b, h, q0, q_end);
   a.init_offsets();
+  if (RING) a.ring_init();
   const int row0 = q0 + pair * 32, row = row0 + a.n;
   const bool active = row0 < q_end;  // wave-uniform
   const int n = a.n_tiles;
   const int last_valid = a.hi - (a.lo + (n - 1) * kBK);
   // the O waves, the less busy ones, issue all the DMA
   if (group == 1) {
-    a.load_k(0, 0);
-    if (n > 1) a.load_k(1, 1);
+    a.template load<true>(0, 0);
+    if (n > 1) a.template load<true>(1, 1);
   }
   if (group == 0) {
     const int rows = q_end - row0;
@@ -1046,8 +1111,8 @@ __device__ __forceinline__ void fwd_half_item(const Params& p, int cl, int bh, i
       a.template mfma_slot<false, true, false>(0, j & 1);
     };
     for (int j = 0; j < n; ++j) {
-      if (j + 2 < n) a.load_k(j + 2, j & 1);
-      a.load_v(j, j & 1);
+      if (j + 2 < n) a.template load<true>(j + 2, j & 1);
+      a.template load<false>(j, j & 1);
       if (j > 0) pv(j - 1);
       wait_vmcnt<0>();
       barrier();
