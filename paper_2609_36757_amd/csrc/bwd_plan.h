@@ -55,11 +55,11 @@ inline int64_t bwd_kv_tiles(const BwdShape& s, int64_t c) {
 }
 
 // Unit costs in thirds of a dK/dV tile (about 0.6 us).  Fitted to the times of
-// the four split choices on eleven shapes (head_dim 64 and 128, 96 to 900
-// units; 8% rms): a dQ tile counts 4/3 of a dK/dV tile, a unit's prologue and
-// epilogue 5 tiles, and 10 when it adds its sums to a zeroed output (2 TB/s of
-// atomic adds, against 4.9 TB/s of a copy).
-constexpr int64_t kBwdUnitCost = 15, kBwdSplitUnitCost = 30;
+// the four split choices on eleven shapes (head_dim 64 and 128, 24 to 900
+// units; 4 to 5% rms): a dQ tile counts 4/3 of a dK/dV tile, a unit's prologue and
+// epilogue 6 tiles, and 10 when it adds its sums to a zeroed output; the adds of
+// all units (2 TB/s, against 4.9 TB/s of a copy) take 2 tiles a unit and CU more.
+constexpr int64_t kBwdUnitCost = 18, kBwdSplitUnitCost = 30, kBwdSplitAddCost = 6;
 inline int64_t bwd_q_cost(int64_t tiles, int64_t split) {
   return 4 * ((tiles + split - 1) / split) + (split > 1 ? kBwdSplitUnitCost : kBwdUnitCost);
 }
@@ -101,7 +101,9 @@ inline int64_t bwd_plan(const BwdShape& s, int n_cu, BwdPlan* p) {
     int64_t span = class_makespan(best, n, n_cu);
     for (int opt = 1; opt < 4; ++opt) {
       const int m = bwd_sorted_classes(s, (opt & 1) ? 2 : 1, (opt & 2) ? 2 : 1, cls);
-      const int64_t t = class_makespan(cls, m, n_cu);
+      int64_t added = 0;
+      for (int k = 0; k < m; ++k) added += (opt & (cls[k].kind ? 2 : 1)) ? cls[k].units : 0;
+      const int64_t t = class_makespan(cls, m, n_cu) + kBwdSplitAddCost * added / n_cu;
       if (25 * t < 24 * span) {  // 4% at least: the model is no better than that
         span = t;
         n = m;
