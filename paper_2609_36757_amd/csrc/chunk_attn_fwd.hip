@@ -9,6 +9,7 @@
 //
 // Work decomposition: one workgroup (8 wave64, 512 threads) per
 // (batch, head, query chunk, 256-row query tile); tiles never straddle a chunk.
+// (Calls with fewer such items than CUs use lower tiles, fwd_plan.h.)
 // Items are dispatched longest first, a class of equal items at a time with the
 // classes spread over all XCDs (5003 tokens in chunks of 1365, W = 2, 16 heads,
 // d = 64: 103.7 -> 84 us against rounds of 256 that gave whole XCDs to one class);
@@ -112,6 +113,7 @@ struct Params {
   int32_t q_st, k_st, v_st, o_st;  // token strides (elements, < 2^22)
   int32_t nq, nkv, chunk_len, q_chunk_offset, window;  // window -1 = unbounded
   int32_t B, H, n_local_chunks, tiles_full, tiles_last, n_items;
+  int32_t item_rows;  // query rows of an item
   float c;  // scale * log2(e)
   int32_t o_bf16;  // 1: O stored as bf16 (round to nearest even), 0: fp32
   // Bounded ring cache (ring step only): key rows are virtual rows over the
@@ -706,7 +708,9 @@ __device__ __forceinline__ void fwd_item(const Params& p, int cl, int bh, int t,
   const int group = a.wave >> 2;  // 0: waves 0-3, 1: waves 4-7 (one wave of each per SIMD)
 
   int b, h, q_end, q0;
-  item_rows<A, D, RING>(p, cl, bh, t, kBQ, a, b, h, q0, q_end);
+  // item lists (SPLIT) always hold 256-row items
+  item_rows<A, D, RING>(p, cl, bh, t, SPLIT ? kBQ : p.item_rows, a, b, h, q0, q_end);
+  if (!SPLIT && q_end - q0 > p.item_rows) q_end = q0 + p.item_rows;
   a.init_offsets();
 
   const int row = q0 + a.wave * 32 + a.n;
@@ -1218,14 +1222,13 @@ hipError_t launch_chunk_attn_fwd(const FwdArgs& a, hipStream_t stream) {
   const int64_t bh = a.B * a.H;
   const ItemShape shape{bh, p.n_local_chunks, p.tiles_full, p.tiles_last, p.chunk_len,
                         p.q_chunk_offset, p.window, p.nkv, kBK};
-  // 128-row items where 256-row ones leave CUs idle
-  const FwdGrid gh = fwd_grid(a.B, a.H, a.nq, L, kHalfRows);
   FwdPlan plan;
-  fwd_plan(shape, gh.tiles_full, gh.tiles_last, (int)a.d, n_cu, &plan);
-  if (plan.half) {
-    p.tiles_full = (int32_t)gh.tiles_full;
-    p.tiles_last = (int32_t)gh.tiles_last;
-    p.n_items = (int32_t)gh.n_items;
+  fwd_plan(shape, a.nq - (g.n_local_chunks - 1) * L, (int)a.d, n_cu, &plan);
+  p.item_rows = plan.rows;
+  if (plan.rows != kBQ) {
+    p.tiles_full = (int32_t)plan.tiles_full;
+    p.tiles_last = (int32_t)plan.tiles_last;
+    p.n_items = plan.tab.first[plan.tab.n];
   } else if (!ring && g.n_items > 0 && g.n_items <= kListMaxItems && n_cu > 0) {
     static PlanCache plans;
     if (plans.plan(shape, (int)g.n_items, n_cu, &lists, &n_groups)) use_lists = &lists;

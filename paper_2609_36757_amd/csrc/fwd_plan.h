@@ -1,5 +1,5 @@
 // Work plan of the forward's plain dispatch (host code, plain C++): the class
-// table, and whether the call runs 128-row or 256-row items.
+// table, and the height of the call's items.
 //
 // A 256-row item keeps both waves of every SIMD at matrix-core and softmax work
 // in turn and has the higher throughput.  A 128-row item, whose SIMD pair shares
@@ -21,8 +21,16 @@ constexpr int kHalfRows = 128;
 
 struct FwdPlan {
   ClassTable tab;
-  bool half;
+  bool half;             // 128-row items (rows = 128)
+  int32_t rows;          // query rows of an item
+  int64_t tiles_full, tiles_last;  // items of a full and of the last chunk
 };
+
+// Heights of a call whose 256-row items all run at once, on no more than the
+// CUs: the lowest that still does.  A CU's time falls a little with its rows
+// (156 items of 256 rows 280 us; 204 of 192 rows 267; 240 of 160 rows 263; fewer
+// waves at the LDS), and the CUs that had no item take the rest.
+constexpr int kLowHeights[] = {160, 192, 224};
 
 // Items per CU up to which 128-row items are considered.
 constexpr int64_t kHalfMaxRounds = 4;
@@ -33,30 +41,42 @@ inline int64_t fwd_cost(int64_t key_tiles, bool half, int d) {
   return (half ? (d == 128 ? 16 : 14) : 25) * key_tiles + 75;
 }
 
-// s: the call with its 256-row tiles; half_full / half_last: 128-row tiles of a
-// full and of the last chunk.
-inline void fwd_plan(const ItemShape& s, int64_t half_full, int64_t half_last, int d, int n_cu, FwdPlan* p) {
-  auto classes = [&](bool half, WorkClass* out) {
-    const int64_t per = s.bh * (half ? half_full : s.tiles_full), last = s.bh * (half ? half_last : s.tiles_last);
-    const int n = make_classes(s.n_local_chunks, per, last, 0, kMaxClasses, out,
-                               [&](int64_t c) { return fwd_cost(chunk_key_tiles(s, c), half, d); });
+// s: the call with its 256-row tiles; last_rows: query rows of its last chunk.
+inline void fwd_plan(const ItemShape& s, int64_t last_rows, int d, int n_cu, FwdPlan* p) {
+  WorkClass cls[2][kMaxClasses];
+  auto classes = [&](int rows, WorkClass* out) {
+    const int64_t last = (last_rows + rows - 1) / rows;
+    const int64_t full = s.n_local_chunks > 1 ? (s.chunk_len + rows - 1) / rows : last;
+    p->half = rows == kHalfRows;
+    p->rows = rows;
+    p->tiles_full = full;
+    p->tiles_last = last;
+    const int n = make_classes(s.n_local_chunks, s.bh * full, s.bh * last, 0, kMaxClasses, out,
+                               [&](int64_t c) { return fwd_cost(chunk_key_tiles(s, c), p->half, d); });
     sort_classes(out, n);
     return n;
   };
-  WorkClass full[kMaxClasses], half[kMaxClasses];
-  const int n = classes(false, full);
-  int64_t units = 0;
-  for (int k = 0; k < n; ++k) units += full[k].units;
-  p->half = false;
+  auto items = [&]() { return s.bh * (p->tiles_last + p->tiles_full * (s.n_local_chunks - 1)); };
+  int n = classes(256, cls[0]);
+  const int64_t units = items();
   if (n_cu > 0 && n_cu <= 256 && units <= kHalfMaxRounds * n_cu) {
-    const int m = classes(true, half);
-    if (25 * class_makespan(half, m, n_cu) < 24 * class_makespan(full, n, n_cu)) {
-      p->half = true;
-      fill_table(half, m, &p->tab);
+    const int64_t span = class_makespan(cls[0], n, n_cu);
+    const int m = classes(kHalfRows, cls[1]);
+    if (25 * class_makespan(cls[1], m, n_cu) < 24 * span) {
+      fill_table(cls[1], m, &p->tab);
       return;
     }
+    if (units <= n_cu)
+      for (int rows : kLowHeights) {
+        n = classes(rows, cls[0]);
+        if (items() <= n_cu) {
+          fill_table(cls[0], n, &p->tab);
+          return;
+        }
+      }
+    n = classes(256, cls[0]);
   }
-  fill_table(full, n, &p->tab);
+  fill_table(cls[0], n, &p->tab);
 }
 
 }  // namespace fastvr

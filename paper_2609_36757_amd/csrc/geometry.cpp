@@ -6,14 +6,14 @@
 namespace fastvr {
 
 // Forward: one work item per (batch, head, query chunk, query tile of
-// `rows` rows); tiles never straddle a chunk.
-FwdGrid fwd_grid(int64_t B, int64_t H, int64_t nq, int64_t chunk_len, int64_t rows) {
+// kFwdRowsPerItem rows); tiles never straddle a chunk.
+FwdGrid fwd_grid(int64_t B, int64_t H, int64_t nq, int64_t chunk_len) {
   FwdGrid g{};
   if (B <= 0 || H <= 0 || nq <= 0 || chunk_len <= 0) return g;
   g.n_local_chunks = (nq + chunk_len - 1) / chunk_len;
   const int64_t last_rows = nq - (g.n_local_chunks - 1) * chunk_len;
-  g.tiles_last = (last_rows + rows - 1) / rows;
-  g.tiles_full = g.n_local_chunks > 1 ? (chunk_len + rows - 1) / rows : g.tiles_last;
+  g.tiles_last = (last_rows + kFwdRowsPerItem - 1) / kFwdRowsPerItem;
+  g.tiles_full = g.n_local_chunks > 1 ? (chunk_len + kFwdRowsPerItem - 1) / kFwdRowsPerItem : g.tiles_last;
   g.n_items = B * H * (g.tiles_last + g.tiles_full * (g.n_local_chunks - 1));
   return g;
 }

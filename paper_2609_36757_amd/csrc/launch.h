@@ -52,7 +52,7 @@ constexpr int64_t kMaxTokenStride = int64_t(1) << 22;
 // CU count of the current device, queried once per device (0 if it cannot be read).
 int device_cu_count();
 
-FwdGrid fwd_grid(int64_t B, int64_t H, int64_t nq, int64_t chunk_len, int64_t rows = kFwdRowsPerItem);
+FwdGrid fwd_grid(int64_t B, int64_t H, int64_t nq, int64_t chunk_len);
 hipError_t launch_chunk_attn_fwd(const FwdArgs& a, hipStream_t stream);
 
 // Backward of one chunk-causal attention call.  All tensors are contiguous

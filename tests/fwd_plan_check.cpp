@@ -21,20 +21,15 @@ using namespace fastvr;
 
 static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-static bool check(int64_t bh, int64_t nq, int64_t nkv, int64_t L, int64_t off, int64_t W, int d, int n_cu = 256) {
+// Rows of the call's items.
+static int check(int64_t bh, int64_t nq, int64_t nkv, int64_t L, int64_t off, int64_t W, int d, int n_cu = 256) {
   if (L > nkv) L = nkv;
   const int64_t nc = cdiv(nq, L), last = nq - (nc - 1) * L;
-  auto tiles = [&](int64_t rows, int64_t& full, int64_t& tail) {
-    tail = cdiv(last, rows);
-    full = nc > 1 ? cdiv(L, rows) : tail;
-  };
-  ItemShape s{bh, nc, 0, 0, L, off, W, nkv, 96};
-  int64_t hf, hl;
-  tiles(256, s.tiles_full, s.tiles_last);
-  tiles(128, hf, hl);
+  ItemShape s{bh, nc, nc > 1 ? cdiv(L, 256) : cdiv(last, 256), cdiv(last, 256), L, off, W, nkv, 96};
   FwdPlan p;
-  fwd_plan(s, hf, hl, d, n_cu, &p);
-  if (!p.half) hf = s.tiles_full, hl = s.tiles_last;
+  fwd_plan(s, last, d, n_cu, &p);
+  const int64_t hl = cdiv(last, p.rows), hf = nc > 1 ? cdiv(L, p.rows) : hl;
+  CHECK(p.half == (p.rows == 128) && p.rows % 32 == 0 && p.tiles_full == hf && p.tiles_last == hl);
   std::set<std::tuple<int64_t, int64_t, int64_t>> seen;
   for (int k = 0; k < p.tab.n; ++k)
     for (int64_t u = 0; u < p.tab.first[k + 1] - p.tab.first[k]; ++u) {
@@ -43,26 +38,32 @@ static bool check(int64_t bh, int64_t nq, int64_t nkv, int64_t L, int64_t off, i
       CHECK(seen.insert({c, u % (bh * t) / t, u % t}).second);
     }
   CHECK((int64_t)seen.size() == bh * (hl + hf * (nc - 1)));
-  return p.half;
+  if (p.rows != 256 && p.rows != 128) CHECK((int64_t)seen.size() <= n_cu);
+  return p.rows;
 }
 
 int main() {
   std::mt19937_64 rng(11);
   auto pick = [&](int64_t lo, int64_t hi) { return lo + (int64_t)(rng() % (uint64_t)(hi - lo + 1)); };
-  int n = 0, halves = 0;
+  int n = 0, halves = 0, low = 0;
   for (; n < 400; ++n) {
     const int64_t nkv = pick(1, 4000), L = pick(1, 900), off = std::min<int64_t>(pick(0, 3), (nkv - 1) / std::min(L, nkv));
-    halves += check(pick(1, 24), pick(1, nkv - off * std::min(L, nkv)), nkv, L, L > nkv ? 0 : off, pick(-1, 4),
-                    n % 2 ? 64 : 128, n % 3 ? 256 : (int)pick(1, 256));
+    const int rows = check(pick(1, 24), pick(1, nkv - off * std::min(L, nkv)), nkv, L, L > nkv ? 0 : off, pick(-1, 4),
+                           n % 2 ? 64 : 128, n % 3 ? 256 : (int)pick(1, 256));
+    halves += rows == 128;
+    low += rows > 128 && rows < 256;
   }
-  CHECK(halves > 40 && halves < 360);
+  CHECK(halves > 40 && halves < 360 && low > 5);
   // 8 and 128 items of 256 rows leave CUs idle; 156 would need two waves of 128-row
-  // items; 768 fill the chip; the shapes of tests/test_gpu_half_items.py
-  CHECK(check(2, 1024, 1024, 256, 0, -1, 64) && check(4, 8192, 8192, 8192, 0, -1, 128));
-  CHECK(!check(12, 3120, 12480, 3120, 3, -1, 128) && !check(12, 16320, 65280, 16320, 3, -1, 128));
+  // items, but 240 of 160 rows still run at once; 768 fill the chip
+  CHECK(check(2, 1024, 1024, 256, 0, -1, 64) == 128 && check(4, 8192, 8192, 8192, 0, -1, 128) == 128);
+  CHECK(check(12, 3120, 12480, 3120, 3, -1, 128) == 160 && check(12, 16320, 65280, 16320, 3, -1, 128) == 256);
+  // the shapes of tests/test_gpu_half_items.py
   for (int d = 64; d <= 128; d += 64) {
-    CHECK(check(2, 900, 900, 259, 0, -1, d) && check(2, 259, 518, 259, 1, 1, d));
-    CHECK(!check(256, 900, 900, 259, 0, -1, d) && !check(512, 259, 518, 259, 1, 1, d));
+    CHECK(check(2, 900, 900, 259, 0, -1, d) == 128 && check(2, 259, 518, 259, 1, 1, d) == 128);
+    CHECK(check(256, 900, 900, 259, 0, -1, d) == 256 && check(512, 259, 518, 259, 1, 1, d) == 256);
+    CHECK(check(80, 650, 1300, 650, 1, -1, d) == 224 && check(62, 650, 1300, 650, 1, -1, d) == 192);
+    CHECK(check(50, 650, 1300, 650, 1, -1, d) == 160);
   }
   std::printf("%d cases ok\n", n);
   return 0;

@@ -1,6 +1,7 @@
-"""128-row against 256-row items of the forward, bit for bit: a small call runs
-128-row items, the same tensors repeated as a large batch 256-row ones
-(tests/fwd_plan_check.cpp checks both plans).  Odd chunk lengths leave ragged
+"""Lower against 256-row items of the forward, bit for bit: a small call runs
+128-row items (160 to 224 rows where those would need a second wave), the same
+tensors repeated as a large batch 256-row ones (tests/fwd_plan_check.cpp checks
+the plans).  Odd chunk lengths leave ragged
 tiles in both heights and a ragged last key tile; interval lengths are even and
 odd numbers of key tiles.  One case of each is also held against the oracle."""
 import numpy as np
@@ -42,6 +43,25 @@ def test_half_items_equal_full_items(dev, d, scale, L, N, off, W, reps):
     assert torch.equal(ob, o.to(torch.bfloat16))
     o_ref, l_ref = run_oracle(q, k, v, L, off, W, scale)
     compare(to_np(o), to_np(lse), o_ref, l_ref, label=f"half items d={d} scale={scale:.3f} off={off}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("bh", [80, 62, 50])
+def test_low_items_equal_full_items(dev, d, bh):
+    """224, 192 and 160 rows (bh = 80, 62, 50) over one ragged chunk of 650 rows."""
+    L, off, H = 650, 1, 2
+    print(f"\n[gpu case] low items: B={bh // H} H={H} d={d} L={L} off={off}", flush=True)
+    q, k, v = make_qkv(1, L, (off + 1) * L, H, d, seed=700 + d)
+    small = [t.to(dev) for t in (q, k, v)]
+    outs = []
+    for reps in (bh // H, 256):
+        x = [t.expand(reps, *t.shape[1:]).contiguous() for t in small]
+        outs.append(fastvr.chunk_attn(*x, chunk_len=L, q_chunk_offset=off))
+    torch.cuda.synchronize()
+    for a, b in zip(*outs):
+        assert torch.equal(a[:1].expand_as(a), a) and torch.equal(a[:1].expand_as(b), b)
+    o_ref, l_ref = run_oracle(q, k, v, L, off, -1, 1 / np.sqrt(d))
+    compare(to_np(outs[0][0][:1]), to_np(outs[0][1][:1]), o_ref, l_ref, label=f"low items d={d} bh={bh}")
 
 
 @pytest.mark.parametrize("d,L", [(128, 260), (64, 264)])
