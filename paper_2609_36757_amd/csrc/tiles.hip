@@ -249,14 +249,16 @@ hipError_t launch_tile_blend(const float* tiles, const void* z_lq, float* out, f
   const int R = overlap > 1 ? (int)overlap : 1;
   const int64_t row_units = Wg * (C / 4);
   const bool narrow = narrow_index(rows, ay, ax, Hg, Wg);
-  // Tiles that fit the 256 MB Infinity Cache are usually still there (the call
-  // that produced them ran just before) and are read through the caches, two
-  // units a thread for more waves: 6 tiles of 8 x 64 x 64 x 48 14.9 -> 11.3 us,
-  // 277 MB of tiles 73.5 -> 62.9 us.  Larger ones are each read exactly once and
-  // streamed past the caches, four units a thread: 1.2 GB 257 against 284 us,
-  // 470 MB 92 against 100 us.  The line is drawn between, at 1.25 times that cache.
-  const bool streamed = B * ay.n * ax.n * T * ay.L * ax.L * C * 4 > ((int64_t)320 << 20);
-  const dim3 grid = row_grid(row_units, rows, streamed ? 4 : 2);
+  // Up to 64 MB of tiles are mostly still in the 256 MB Infinity Cache when the call
+  // follows the one that produced them, and are read through the caches; larger
+  // ones, each read exactly once, past them.  Two units a thread (more waves), four
+  // beyond 320 MB.  Measured with four inputs in turn, against non-temporal loads
+  // of four units for all sizes: 47 MB of tiles 15.8 -> 11.8 us (14.7 past the
+  // caches); 201 MB 62.4 -> 47.7 us (51.4 through them); 277 MB 74.0 -> 69.7 us; at
+  // 390 MB two and four units are equal, at 1.2 GB four take 257 and two 266 us.
+  const int64_t tile_bytes = B * ay.n * ax.n * T * ay.L * ax.L * C * 4;
+  const bool cached = tile_bytes <= ((int64_t)64 << 20), four = tile_bytes > ((int64_t)320 << 20);
+  const dim3 grid = row_grid(row_units, rows, four ? 4 : 2);
   const uint16_t* zp = static_cast<const uint16_t*>(z_lq);
   const float ns = z_lq != nullptr ? -sigma : 0.f;
 #define FASTVR_BLEND_LAUNCH(ZV, IT, UV, SV)                                                                             \
@@ -268,11 +270,13 @@ hipError_t launch_tile_blend(const float* tiles, const void* z_lq, float* out, f
     else FASTVR_BLEND_LAUNCH(ZV, uint64_t, UV, SV);         \
   } while (0)
   if (z_lq != nullptr) {
-    if (streamed) FASTVR_BLEND_INDEX(true, 4, true);
-    else FASTVR_BLEND_INDEX(true, 2, false);
+    if (four) FASTVR_BLEND_INDEX(true, 4, true);
+    else if (cached) FASTVR_BLEND_INDEX(true, 2, false);
+    else FASTVR_BLEND_INDEX(true, 2, true);
   } else {
-    if (streamed) FASTVR_BLEND_INDEX(false, 4, true);
-    else FASTVR_BLEND_INDEX(false, 2, false);
+    if (four) FASTVR_BLEND_INDEX(false, 4, true);
+    else if (cached) FASTVR_BLEND_INDEX(false, 2, false);
+    else FASTVR_BLEND_INDEX(false, 2, true);
   }
 #undef FASTVR_BLEND_INDEX
 #undef FASTVR_BLEND_LAUNCH

@@ -1,7 +1,7 @@
 """The gather around the edges of its 768-unit segments and in grids of one tile,
-bit for bit against slicing; the blend of a tile tensor past the 320 MB line (read
-past the caches) bit for bit against the same field blended batch by batch (read
-through them)."""
+bit for bit against slicing; the blend of a tile tensor past the 320 MB line (four
+units a thread) bit for bit against the same field blended in pairs (two units)
+and one by one (at the 64 MB line, read through the caches)."""
 import pytest
 import torch
 
@@ -36,16 +36,17 @@ def test_gather_equals_slices(dev, Hg, Wg, C, tile, overlap):
 
 
 @pytest.mark.parametrize("update", [False, True])
-def test_streamed_blend_equals_cached(dev, update):
+def test_blend_paths_agree(dev, update):
     B, T, Hg, Wg, C = 6, 4, 70, 90, 256
     print(f"\n[gpu case] blend B={B} T={T} {Hg}x{Wg} C={C} update={update}", flush=True)
     ny, Ly = fastvr.tile_axis(Hg, 64, 16)
     nx, Lx = fastvr.tile_axis(Wg, 64, 16)
     tiles = torch.randn((B, ny * nx, T, Ly, Lx, C), device=dev)
-    assert tiles.numel() * 4 > 320 << 20 > tiles[0].numel() * 4
+    assert tiles.numel() * 4 > 320 << 20 > tiles[:2].numel() * 4 > 64 << 20 >= tiles[0].numel() * 4
     z = torch.randn((B, T, Hg, Wg, C), device=dev).to(torch.bfloat16) if update else None
     whole = fastvr.tile_blend(tiles, Hg, Wg, z_lq=z, sigma=0.4)
-    for b in range(B):
-        one = fastvr.tile_blend(tiles[b:b + 1], Hg, Wg, z_lq=z[b:b + 1] if update else None, sigma=0.4)
-        torch.cuda.synchronize()
-        assert torch.equal(one[0], whole[b]), b
+    for n in (1, 2):
+        for b in range(0, B, n):
+            part = fastvr.tile_blend(tiles[b:b + n], Hg, Wg, z_lq=z[b:b + n] if update else None, sigma=0.4)
+            torch.cuda.synchronize()
+            assert torch.equal(part, whole[b:b + n]), (n, b)
