@@ -295,7 +295,7 @@ def tiled_1080p(torch, fastvr, metrics, dev, cur, qd, kd, vd, w):
     gb = lambda nbytes, ms: round(nbytes / (ms * 1e-3) / 1e9, 1)
     tile_bytes = tiles[0].numel() * 2
     return {"tiles": f"{nt} ({Ly} x {Lx}) per frame, {N} tokens per tile",
-            "gather_qkv_ms": round(ms_g, 4), "gather_GB/s": gb(3 * 2 * tile_bytes, ms_g),
+            "gather_qkv_ms": round(ms_g, 4), "gather_GB/s": gb(3 * (2 * qg.numel() + tile_bytes), ms_g),
             "attention_ms": round(ms_a, 4), "attention_tflops": round(f_a / (ms_a * 1e-3) / 1e12, 2),
             "blend_o_ms": round(ms_b, 4), "blend_GB/s": gb(o.numel() * 4 + out.numel() * 4, ms_b),
             "blend_update_latent_ms": round(ms_u, 5),
