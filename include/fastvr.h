@@ -175,6 +175,9 @@ fastvr_status fastvr_chunk_attn_ring_step(const void* q_new, const void* k_new, 
  * of the forward call that produced o and lse.  Two kernels run in order on
  * `stream` (row statistics, then all gradients).  Each sum runs in a fixed order,
  * or as two such parts added into a zero, so results are reproducible bit for bit.
+ * The two parts are added atomically, which only the device's own coarse-grained
+ * memory defines: a call whose dq, dk or dv lie elsewhere (pinned, managed or
+ * fine-grained memory, a peer's) sums without parts.
  *
  * Preconditions (else FASTVR_ERR_INVALID_ARGUMENT unless noted):
  *  - q, k, v, dout, o, dq, dk, dv non-NULL and 16-byte aligned (q, dout, o, dq

@@ -90,14 +90,15 @@ inline int bwd_sorted_classes(const BwdShape& s, int64_t q_split, int64_t kv_spl
 // 8000 keys) and below splits gained 5 to 40%.
 constexpr int64_t kBwdSplitMaxRounds = 4;
 
-// Fills the plan; returns the number of units (the grid).
-inline int64_t bwd_plan(const BwdShape& s, int n_cu, BwdPlan* p) {
+// Fills the plan; returns the number of units (the grid).  may_split: the outputs
+// lie in memory that the halves' atomic adds are defined on.
+inline int64_t bwd_plan(const BwdShape& s, int n_cu, bool may_split, BwdPlan* p) {
   WorkClass cls[kMaxClasses], best[kMaxClasses];
   int n = bwd_sorted_classes(s, 1, 1, best);
   p->q_split = p->kv_split = 1;
   int64_t units = 0;
   for (int k = 0; k < n; ++k) units += best[k].units;
-  if (n_cu > 0 && n_cu <= 256 && units <= kBwdSplitMaxRounds * n_cu) {
+  if (may_split && n_cu > 0 && n_cu <= 256 && units <= kBwdSplitMaxRounds * n_cu) {
     int64_t span = class_makespan(best, n, n_cu);
     for (int opt = 1; opt < 4; ++opt) {
       const int m = bwd_sorted_classes(s, (opt & 1) ? 2 : 1, (opt & 2) ? 2 : 1, cls);

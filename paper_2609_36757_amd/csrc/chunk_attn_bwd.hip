@@ -922,6 +922,20 @@ __global__ __launch_bounds__(kBwdThreads) void chunk_attn_bwd_kernel(const BwdPa
     dq_unit<D, SPLIT>(p, c0 + ci, bh, t, half, split, smem);
 }
 
+// Whether p lies in the current device's own coarse-grained memory.  Only there
+// is the hardware's fp32 atomic add defined: on pinned, managed or fine-grained
+// memory and on a peer's it may be dropped, while plain stores work, so split
+// units are for such outputs only.
+bool takes_atomic_adds(const void* p) {
+  hipPointerAttribute_t at;
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();  // memory that HIP does not know: not an error of this call
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && !at.isManaged && at.allocationFlags == 0 && at.device == dev;
+}
+
 template <int D>
 hipError_t launch_bwd_t(BwdParams& p, const BwdPlan& plan, int64_t n_units, hipStream_t stream) {
   const int64_t bh = (int64_t)p.B * p.H;
@@ -983,7 +997,11 @@ hipError_t launch_chunk_attn_bwd(const BwdArgs& a, hipStream_t stream) {
   const BwdShape shape{a.B * a.H, g.q.n_local_chunks, g.q.tiles_full, g.q.tiles_last, g.n_kchunks, g.kblocks_full,
                        g.kblocks_last, L, a.q_chunk_offset, p.window, a.nq, a.nkv};
   BwdPlan plan;
-  const int64_t n_units = bwd_plan(shape, device_cu_count(), &plan);
+  const int n_cu = device_cu_count();
+  int64_t n_units = bwd_plan(shape, n_cu, true, &plan);
+  if ((plan.q_split > 1 && !takes_atomic_adds(a.dq)) ||
+      (plan.kv_split > 1 && !(takes_atomic_adds(a.dk) && takes_atomic_adds(a.dv))))
+    n_units = bwd_plan(shape, n_cu, false, &plan);
   p.unit_base = 0;
   if (a.d == 128) return launch_bwd_t<128>(p, plan, n_units, stream);
   return launch_bwd_t<64>(p, plan, n_units, stream);

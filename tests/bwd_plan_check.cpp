@@ -45,7 +45,7 @@ static BwdShape make(int64_t bh, int64_t nq, int64_t nkv, int64_t L, int64_t off
 
 static void check(const BwdShape& s, int n_cu) {
   BwdPlan p;
-  const int64_t n = bwd_plan(s, n_cu, &p);
+  const int64_t n = bwd_plan(s, n_cu, true, &p);
   CHECK(p.tab.n >= 1 && p.tab.n <= kMaxClasses && p.tab.first[0] == 0 && p.tab.first[p.tab.n] == n);
   CHECK((p.q_split == 1 || p.q_split == 2) && (p.kv_split == 1 || p.kv_split == 2));
   std::set<std::tuple<int, int64_t, int64_t, int64_t, int64_t>> seen;
@@ -96,8 +96,11 @@ int main() {
                            make(1, 2105, 2105, 100, 0, -1), make(1, 1300, 3900, 1300, 2, 0)};
   for (int i = 0; i < 5; ++i) {
     BwdPlan p;
-    bwd_plan(gpu[i], 256, &p);
+    bwd_plan(gpu[i], 256, true, &p);
     CHECK(p.q_split == 2 && p.kv_split == (i < 2 ? 1 : 2));
+    // outputs that take no atomic adds: no halves
+    bwd_plan(gpu[i], 256, false, &p);
+    CHECK(p.q_split == 1 && p.kv_split == 1);
   }
   // the grouped schedule against CU-by-CU simulation
   for (int i = 0; i < 200; ++i, ++cases) {

@@ -49,3 +49,25 @@ def test_bwd_split_units(dev, case):  # noqa: F811
         compare_grad(n, to_np(g), r, s, name)
     seen = oracle.visibility_mask(nq, nkv, L, off, W).any(axis=0)
     assert (to_np(runs[0][1])[:, ~seen] == 0).all() and (to_np(runs[0][2])[:, ~seen] == 0).all()
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_bwd_outputs_in_pinned_host_memory(dev, case):  # noqa: F811
+    """Outputs that are not the GPU's own memory take no atomic adds: the plan
+    must not cut units in two, so pinned host outputs hold the bits of the
+    unsplit units, which the same heads repeated as a large call run."""
+    name, B, H, d, nq, L, off, W = case
+    nkv = off * L + nq
+    reps = 1 + 4 * 256 // (B * H)  # one 256-row query tile per head alone is then over 4 units per CU
+    print(f"\n[gpu case] bwd pinned outputs {name} B={B} H={H} d={d} Nq={nq} L={L} reps={reps}", flush=True)
+    kw = dict(chunk_len=L, q_chunk_offset=off, window_chunks=W, scale=default_scale(d))
+    q, k, v = (t.to(dev) for t in make_qkv(B, nq, nkv, H, d, 900 + nq))
+    do = _draw_do(B, nq, H, d, 901 + nq).to(dev)
+    o, lse = fastvr.chunk_attn(q, k, v, **kw)
+    host = [torch.full((B, n, H, d), float("nan"), pin_memory=True) for n in (nq, nkv, nkv)]
+    fastvr.chunk_attn_bwd(q, k, v, o, lse, do, dq=host[0], dk=host[1], dv=host[2], **kw)
+    wide = [t.repeat(1, 1, reps, 1) for t in (q, k, v, o)]
+    ref = fastvr.chunk_attn_bwd(*wide, lse.repeat(1, reps, 1), do.repeat(1, 1, reps, 1), **kw)
+    torch.cuda.synchronize()
+    for n, a, b in zip(("dq", "dk", "dv"), host, ref):
+        assert torch.equal(a, b[:, :, :H].cpu()), (name, n)
