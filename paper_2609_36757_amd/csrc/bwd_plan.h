@@ -72,7 +72,10 @@ inline int bwd_classes(const BwdShape& s, bool kv, int64_t split, WorkClass* out
   const int64_t n = kv ? s.n_kchunks : s.n_qchunks;
   const int64_t per = (kv ? s.kblocks_full : s.tiles_full) * s.bh * split;
   const int64_t per_last = (kv ? s.kblocks_last : s.tiles_last) * s.bh * split;
-  return make_classes(n, per, per_last, kv ? 1 : 0, kMaxClasses / 2, out, [&](int64_t c) {
+  // a query chunk sees more keys the later it is, up to the window; a key chunk is
+  // seen by more queries up to the first query chunk, and by fewer after it
+  const int64_t peak = kv ? s.q_chunk_offset : n;
+  return make_classes(n, per, per_last, kv ? 1 : 0, kMaxClasses / 2, peak, out, [&](int64_t c) {
     return kv ? bwd_kv_cost(bwd_kv_tiles(s, c), split) : bwd_q_cost(bwd_q_tiles(s, c), split);
   });
 }

@@ -51,7 +51,7 @@ inline void fwd_plan(const ItemShape& s, int64_t last_rows, int d, int n_cu, Fwd
     p->rows = rows;
     p->tiles_full = full;
     p->tiles_last = last;
-    const int n = make_classes(s.n_local_chunks, s.bh * full, s.bh * last, 0, kMaxClasses, out,
+    const int n = make_classes(s.n_local_chunks, s.bh * full, s.bh * last, 0, kMaxClasses, s.n_local_chunks, out,
                                [&](int64_t c) { return fwd_cost(chunk_key_tiles(s, c), p->half, d); });
     sort_classes(out, n);
     return n;
