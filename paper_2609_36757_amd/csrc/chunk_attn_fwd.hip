@@ -79,9 +79,10 @@ constexpr int kStages = 3;                // LDS buffers per operand
 //  FASTVR_PRIO       raise the wave priority during matrix-core slots
 //  FASTVR_AHEAD      MFMA operand reads kept in flight ahead of their MFMA
 //  FASTVR_VALU_PER   row-statistics instructions placed after each P.V MFMA
-//  FASTVR_DMA_SPLIT  1: the four vector-ALU waves of a slot issue its DMA; 0: all eight
-//                    (with 96-key tiles only for head_dim 128: a d = 64 tile is 12
-//                    DMA instructions, not a multiple of eight)
+//  FASTVR_DMA_SPLIT  256-row items, 1: the four vector-ALU waves of a slot issue its DMA;
+//                    0: all eight (with 96-key tiles only for head_dim 128: a d = 64 tile
+//                    is 12 DMA instructions, not a multiple of eight).  In 128-row items
+//                    the four O waves issue it either way.
 #ifndef FASTVR_SCHED
 #define FASTVR_SCHED 1
 #endif
@@ -180,13 +181,13 @@ __device__ __forceinline__ void decode_block(const Params& p, const ClassTable& 
 // arithmetic either way (outputs are bit-identical).  The per-CU list kernel
 // uses it: it moves work out of the matrix-core slot, which helps the short
 // items of those calls, and it keeps that kernel within its registers.
-template <int D, bool NEG, bool RING, bool SPLIT = false>
+// DMA_WAVES: waves issuing the DMA of one tile: all 8, or the 4 waves that run the
+// softmax in that slot, each with twice the instructions.
+template <int D, bool NEG, bool RING, bool SPLIT = false, int DMA_WAVES = FASTVR_DMA_SPLIT ? kWaves / 2 : kWaves>
 struct Attn {
   static constexpr int kChunks = D / 8;                        // 16-byte chunks per key row
   static constexpr int kStage = kBK * D;                       // bf16 elements per stage (K or V)
-  // Waves issuing the DMA of one tile: all 8, or (split) the 4 waves that run
-  // the softmax in that slot, each with twice the instructions.
-  static constexpr int kDmaWaves = FASTVR_DMA_SPLIT ? kWaves / 2 : kWaves;
+  static constexpr int kDmaWaves = DMA_WAVES;
   static constexpr int kDmaPer = kBK * kChunks / (64 * kDmaWaves);  // DMA instructions per issuing wave per tile
   static constexpr int kLdsElems = 2 * kStages * kStage;
   static_assert(kDmaPer >= 1 && kChunks >= 8, "head_dim must be 64 or 128");
@@ -909,8 +910,8 @@ template <int D>
 constexpr int kHalfLds = 2 * 2 * kBK * D * 2 + 2 * kHalfP<D> * 16 + 3 * kHalfRows * 4;  // bytes
 
 template <int D, bool NEG, bool RING>
-struct HalfAttn : Attn<D, NEG, RING> {
-  using Base = Attn<D, NEG, RING>;
+struct HalfAttn : Attn<D, NEG, RING, false, kWaves / 2> {
+  using Base = Attn<D, NEG, RING, false, kWaves / 2>;
   // Where the tiles of a ring step have got to: the chunk of the last tile
   // loaded, as the address its virtual row 0 would have (row r at base + r * st)
   // and the virtual row after its last full row.  Tiles are loaded in order, so
