@@ -54,6 +54,19 @@ inline int64_t bwd_kv_tiles(const BwdShape& s, int64_t c) {
   return qhi > qlo ? (qhi - qlo + kBwdTile - 1) / kBwdTile : 0;
 }
 
+// Narrows rows lo .. hi - 1, the summed axis of a unit cut in two, to part `half`:
+// whole tiles, the first part the longer.  False if nothing is left.  (The kernel
+// calls it too: a constexpr function is compiled for host and device.)
+constexpr bool bwd_half_rows(int half, int& lo, int& hi) {
+  constexpr int kTile = (int)kBwdTile;
+  const int mid = lo + ((hi - lo + kTile - 1) / kTile + 1) / 2 * kTile;
+  if (half == 0)
+    hi = mid < hi ? mid : hi;
+  else
+    lo = mid;
+  return lo < hi;
+}
+
 // Unit costs in thirds of a dK/dV tile (about 0.6 us).  Fitted to the times of
 // the four split choices on eleven shapes (head_dim 64 and 128, 24 to 900
 // units; 4 to 5% rms): a dQ tile counts 4/3 of a dK/dV tile, a unit's prologue and

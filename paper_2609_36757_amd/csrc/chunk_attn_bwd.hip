@@ -353,15 +353,7 @@ __device__ __forceinline__ void dq_unit(const BwdParams& p, int cl, int bh, int 
   const int cg = p.q_chunk_offset + cl;
   int lo = (p.window >= 0 && cg > p.window) ? (cg - p.window) * L : 0;
   int hi = (L < p.nkv - cg * L) ? (cg + 1) * L : p.nkv;
-  if (SPLIT && split == 2) {
-    const int mid = lo + ((hi - lo + kTile - 1) / kTile + 1) / 2 * kTile;
-    if (half == 0)
-      hi = mid < hi ? mid : hi;
-    else if (mid < hi)
-      lo = mid;
-    else
-      return;  // a single tile: the first half has it
-  }
+  if (SPLIT && split == 2 && !bwd_half_rows(half, lo, hi)) return;  // a single tile: the first half has it
   const int n_tiles = (hi - lo + kTile - 1) / kTile;
   const int st = p.st;
   const uint16_t* kb = p.k + (int64_t)b * p.kv_sb + (int64_t)h * D;
@@ -771,14 +763,7 @@ __device__ __forceinline__ void dkv_unit(const BwdParams& p, int ck, int bh, int
   int qlo = cl_lo * L;
   int qhi = cl_hi * L;
   if (qhi > p.nq) qhi = p.nq;
-  if (SPLIT && split == 2) {
-    const int mid = qlo + ((qhi - qlo + kTile - 1) / kTile + 1) / 2 * kTile;
-    if (half == 0)
-      qhi = mid < qhi ? mid : qhi;
-    else
-      qlo = mid;
-    if (qlo >= qhi) return;  // nothing to add to the zeroed output
-  }
+  if (SPLIT && split == 2 && !bwd_half_rows(half, qlo, qhi)) return;  // nothing to add to the zeroed output
   const int n_tiles = qhi > qlo ? (qhi - qlo + kTile - 1) / kTile : 0;
   const int st = p.st;
   const uint16_t* qb = p.q + (int64_t)b * p.q_sb + (int64_t)h * D;

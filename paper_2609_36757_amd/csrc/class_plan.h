@@ -23,6 +23,19 @@ struct ClassTable {
   int32_t first[kMaxClasses + 1];
 };
 
+// Workgroups go to the 8 XCDs round-robin; within each round of 256 workgroups
+// of a class (the last one may be shorter), each XCD gets consecutive units
+// (neighbouring tiles of one stream share its L2).  i: index within the class of
+// n units.  Rounds over all units instead would give whole XCDs to one class.
+// (Kernel code; constexpr compiles it for the host as well.)
+constexpr int xcd_unit(int i, int n) {
+  constexpr int kRound = 256;
+  const int r0 = i / kRound * kRound, w = i - r0;
+  const int m = (n - r0 < kRound) ? n - r0 : kRound;  // units of this round
+  const int x = w & 7, per = m >> 3, rem = m & 7;
+  return r0 + x * per + (x < rem ? x : rem) + (w >> 3);
+}
+
 struct WorkClass {
   int64_t cost, units;  // cost of one item, items
   int32_t c0, nc, kind;

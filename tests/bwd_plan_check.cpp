@@ -1,7 +1,7 @@
 // CPU check of the backward's work plan (csrc/bwd_plan.h): over seeded shapes,
 // every (kind, chunk, batch * head, block, half) is decoded from exactly one
-// unit index, the halves of a split tile every streamed tile once, classes are
-// ordered longest first, and the grouped makespan equals a plain simulation.
+// unit index, the halves of a split unit hold every streamed tile once, classes
+// are ordered longest first, and the grouped makespan equals a plain simulation.
 #include "bwd_plan.h"
 
 #include <cstdio>
@@ -49,15 +49,20 @@ static void check(const BwdShape& s, int n_cu) {
   CHECK(p.tab.n >= 1 && p.tab.n <= kMaxClasses && p.tab.first[0] == 0 && p.tab.first[p.tab.n] == n);
   CHECK((p.q_split == 1 || p.q_split == 2) && (p.kv_split == 1 || p.kv_split == 2));
   std::set<std::tuple<int, int64_t, int64_t, int64_t, int64_t>> seen;
+  // the table is the sorted classes, by the cost they were sorted by
+  WorkClass cls[kMaxClasses];
+  CHECK(bwd_sorted_classes(s, p.q_split, p.kv_split, cls) == p.tab.n);
   int64_t prev = INT64_MAX;
   for (int k = 0; k < p.tab.n; ++k) {
+    CHECK(cls[k].cost <= prev && cls[k].c0 == p.tab.c0[k] && cls[k].nc == p.tab.nc[k] && cls[k].kind == p.tab.kind[k]);
+    prev = cls[k].cost;
     const bool kv = p.tab.kind[k] != 0;
     const int64_t split = kv ? p.kv_split : p.q_split, last = (kv ? s.n_kchunks : s.n_qchunks) - 1;
     const int64_t blocks = kv ? (p.tab.c0[k] == last ? s.kblocks_last : s.kblocks_full)
                               : (p.tab.c0[k] == last ? s.tiles_last : s.tiles_full);
     int64_t longest = 0;
     for (int64_t u = p.tab.first[k]; u < p.tab.first[k + 1]; ++u) {
-      int64_t r = u - p.tab.first[k];
+      int64_t r = xcd_unit((int)(u - p.tab.first[k]), p.tab.first[k + 1] - p.tab.first[k]);
       const int64_t per_bh = blocks * split, per_c = per_bh * s.bh;
       const int64_t c = p.tab.c0[k] + r / per_c;
       CHECK(r / per_c < p.tab.nc[k]);
@@ -67,16 +72,42 @@ static void check(const BwdShape& s, int n_cu) {
       CHECK(seen.insert({kv ? 1 : 0, c, bh, half, t}).second);
       longest = std::max(longest, kv ? bwd_kv_cost(bwd_kv_tiles(s, c), split) : bwd_q_cost(bwd_q_tiles(s, c), split));
     }
-    CHECK(longest <= prev || s.n_qchunks > 8);  // grouped chunks may be unequal
-    prev = longest;
+    // a class of one run of equal chunks costs what each of its units does
+    const int64_t n_runs_max = kMaxClasses / 2;
+    if ((kv ? s.n_kchunks : s.n_qchunks) <= n_runs_max) CHECK(longest == cls[k].cost);
   }
   const int64_t q_units = s.n_qchunks ? s.bh * p.q_split * (s.tiles_last + s.tiles_full * (s.n_qchunks - 1)) : 0;
   const int64_t kv_units = s.bh * p.kv_split * (s.kblocks_last + s.kblocks_full * (s.n_kchunks - 1));
   CHECK(n == q_units + kv_units && (int64_t)seen.size() == n);
 }
 
+// The two parts of rows lo .. hi - 1: every row once, the first from lo in whole
+// tiles unless it is alone, neither more than a tile longer than the other.
+static void check_halves(int lo, int hi) {
+  int a0 = lo, a1 = hi, b0 = lo, b1 = hi;
+  const bool a = bwd_half_rows(0, a0, a1), b = bwd_half_rows(1, b0, b1);
+  CHECK(a == (lo < hi) && b == (cdiv(hi - lo, kBwdTile) > 1));
+  if (!a) return;
+  CHECK(a0 == lo && a1 == (b ? b0 : hi));
+  if (!b) return;
+  CHECK(b1 == hi && (a1 - a0) % kBwdTile == 0);
+  const int64_t ta = cdiv(a1 - a0, kBwdTile), tb = cdiv(b1 - b0, kBwdTile);
+  CHECK(ta + tb == cdiv(hi - lo, kBwdTile) && (ta == tb || ta == tb + 1));
+}
+
 int main() {
   std::mt19937_64 rng(7);
+  for (int lo : {0, 1, 63, 230, 5000})
+    for (int n = 0; n <= 1200; ++n) check_halves(lo, lo + n);
+  // the workgroup remap: a permutation, within each round of 256, for every class size
+  for (int n = 1; n <= 1100; ++n) {
+    std::vector<char> hit(n, 0);
+    for (int i = 0; i < n; ++i) {
+      const int u = xcd_unit(i, n);
+      CHECK(u >= 0 && u < n && u / 256 == i / 256 && !hit[u]);
+      hit[u] = 1;
+    }
+  }
   auto pick = [&](int64_t lo, int64_t hi) { return lo + (int64_t)(rng() % (uint64_t)(hi - lo + 1)); };
   int cases = 0;
   check(make(2, 1024, 1024, 256, 0, -1), 256), ++cases;

@@ -32,7 +32,8 @@ static int check(int64_t bh, int64_t nq, int64_t nkv, int64_t L, int64_t off, in
   CHECK(p.half == (p.rows == 128) && p.rows % 32 == 0 && p.tiles_full == hf && p.tiles_last == hl);
   std::set<std::tuple<int64_t, int64_t, int64_t>> seen;
   for (int k = 0; k < p.tab.n; ++k)
-    for (int64_t u = 0; u < p.tab.first[k + 1] - p.tab.first[k]; ++u) {
+    for (int i = 0; i < p.tab.first[k + 1] - p.tab.first[k]; ++i) {
+      const int64_t u = xcd_unit(i, p.tab.first[k + 1] - p.tab.first[k]);
       const int64_t t = p.tab.c0[k] == nc - 1 ? hl : hf, c = p.tab.c0[k] + u / (bh * t);
       CHECK(c < p.tab.c0[k] + p.tab.nc[k] && c < nc);
       CHECK(seen.insert({c, u % (bh * t) / t, u % t}).second);
