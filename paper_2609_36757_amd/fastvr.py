@@ -164,14 +164,19 @@ def tile_blend_update_raw(v_tiles, z_lq, z_hat, sigma, B, T, Hg, Wg, C, tile, ov
 
 # The checks and allocations below are on the path of calls whose kernels take
 # 5 to 20 us.  Measured on the host: torch.cuda.current_stream() 2.8 us against
-# 0.1 us for its raw handle; torch.empty(..., device=...) 1.8 us against 1.3 to
+# 0.1 us for its raw handle (two private functions of torch, so a torch without
+# them takes the public way); torch.empty(..., device=...) 1.8 us against 1.3 to
 # 1.6 us for empty_like / new_empty.
 
 def _stream_handle(stream):
     if stream is not None:
         return stream.cuda_stream
-    from torch import _C
-    return _C._cuda_getCurrentRawStream(_C._cuda_getDevice())  # current stream of the current device
+    import torch
+    try:
+        raw, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(device())  # current stream of the current device
 
 
 def _bnhd_strides(t, name):
