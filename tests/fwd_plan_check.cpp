@@ -65,6 +65,19 @@ int main() {
     CHECK(check(256, 900, 900, 259, 0, -1, d) == 256 && check(512, 259, 518, 259, 1, 1, d) == 256);
     CHECK(check(80, 650, 1300, 650, 1, -1, d) == 224 && check(62, 650, 1300, 650, 1, -1, d) == 192);
     CHECK(check(50, 650, 1300, 650, 1, -1, d) == 160);
+    // its ring steps: chunk 3 with chunk 2 in the ring
+    const int64_t L = d == 128 ? 260 : 264;
+    CHECK(check(2, 200, L + 200, L, 1, 1, d) == 128 && check(512, 200, L + 200, L, 1, 1, d) == 256);
+    CHECK(check(80, 650, 1306, 656, 1, 1, d) == 224 && check(62, 650, 1306, 656, 1, 1, d) == 192);
+    CHECK(check(50, 650, 1306, 656, 1, 1, d) == 160 && check(512, 650, 1306, 656, 1, 1, d) == 256);
+  }
+  // the far streaming chunk of tests/test_gpu_full_items.py: one 256-row item per CU
+  CHECK(check(2, 32768, 258 * 32768, 32768, 257, 1, 128) == 256);
+  // more than four 256-row items per CU (tests/test_gpu_full_items.py: over 1024 heads)
+  for (int i = 0; i < 60; ++i, ++n) {
+    const int64_t nkv = pick(1, 1500), L = pick(1, 900), off = std::min<int64_t>(pick(0, 3), (nkv - 1) / std::min(L, nkv));
+    CHECK(check(pick(1025, 1028), pick(1, nkv - off * std::min(L, nkv)), nkv, L, L > nkv ? 0 : off, pick(-1, 4),
+                i % 2 ? 64 : 128) == 256);
   }
   std::printf("%d cases ok\n", n);
   return 0;

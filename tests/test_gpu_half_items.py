@@ -64,6 +64,66 @@ def test_low_items_equal_full_items(dev, d, bh):
     compare(to_np(outs[0][0][:1]), to_np(outs[0][1][:1]), o_ref, l_ref, label=f"low items d={d} bh={bh}")
 
 
+@pytest.mark.parametrize("d,scale", [(64, 0.125), (64, -0.2), (128, 1 / np.sqrt(128)), (128, -0.08)])
+@pytest.mark.parametrize("bh", [80, 62, 50])
+def test_low_items_strided_bf16(dev, bh, d, scale):
+    """The same heights on views of a cache whose rows past the filled ones are NaN,
+    a strided q, O as bf16 into a strided view, and both signs of the scale."""
+    L, off, H, cap = 650, 1, 2, 1400
+    n = (off + 1) * L
+    print(f"\n[gpu case] low items strided: B={bh // H} H={H} d={d} L={L} off={off} scale={scale:.3f}", flush=True)
+    q, k, v = make_qkv(1, L, n, H, d, seed=720 + d)
+    kw = dict(chunk_len=L, q_chunk_offset=off, scale=scale)
+    outs = []
+    for reps in (bh // H, 256):
+        views = []
+        for t in (q, k, v):
+            buf = torch.full((reps, cap, H, d), float("nan"), dtype=torch.bfloat16, device=dev)
+            buf[:, :t.shape[1]] = t.to(dev)
+            views.append(buf[:, :t.shape[1]])
+        big = torch.full((reps, L + 9, H, d), float("nan"), dtype=torch.bfloat16, device=dev)
+        o, lse = fastvr.chunk_attn(*views, **kw)
+        _, lse_b = fastvr.chunk_attn(*views, out=big[:, 3:3 + L], **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(big[:, 3:3 + L], o.to(torch.bfloat16)) and torch.equal(lse_b, lse)
+        assert torch.isnan(big[:, :3].float()).all() and torch.isnan(big[:, 3 + L:].float()).all()
+        outs.append((o, lse))
+    for a, b in zip(*outs):
+        assert torch.equal(a[:1].expand_as(a), a) and torch.equal(a[:1].expand_as(b), b)
+    o_ref, l_ref = run_oracle(q, k, v, L, off, -1, scale)
+    compare(to_np(outs[0][0][:1]), to_np(outs[0][1][:1]), o_ref, l_ref, label=f"low items strided d={d} bh={bh}")
+
+
+@pytest.mark.parametrize("d,scale", [(64, -0.2), (128, 1 / np.sqrt(128))])
+@pytest.mark.parametrize("bh", [80, 62, 50])
+def test_low_items_ring_step(dev, bh, d, scale):
+    """The ring step at these heights, whose workgroups share the append: outputs and
+    ring against a large batch (256-row items), the replaced slot NaN before."""
+    H, L, W, c, n_new = 2, 656, 1, 3, 650
+    print(f"\n[gpu case] low items ring: B={bh // H} H={H} d={d} L={L} W={W} n_new={n_new}", flush=True)
+    q, k, v = (t.to(dev) for t in make_qkv(1, n_new, n_new, H, d, seed=740 + d))
+    _, rk, rv = (t.to(dev) for t in make_qkv(1, 1, (W + 1) * L, H, d, seed=741 + d))
+    slot = c % (W + 1) * L
+    rk[:, slot:slot + L] = float("nan")
+    rv[:, slot:slot + L] = float("nan")
+    outs = []
+    for reps in (bh // H, 256):
+        args = [t.expand(reps, *t.shape[1:]).contiguous() for t in (q, k, v, rk, rv)]
+        o, lse = fastvr.chunk_attn_ring_step(*args, chunk_len=L, chunk_index=c, window_chunks=W, scale=scale)
+        torch.cuda.synchronize()
+        for ring, old, new in ((args[3], rk, k), (args[4], rv, v)):
+            want = old.clone()
+            want[:, slot:slot + n_new] = new
+            assert torch.equal(ring.view(torch.int16), want.view(torch.int16).expand(reps, *ring.shape[1:]))
+        outs.append((o, lse))
+    for a, b in zip(*outs):
+        assert torch.equal(a[:1].expand_as(a), a) and torch.equal(a[:1].expand_as(b), b)
+    prev = slice(L - slot, 2 * L - slot)  # the other slot holds chunk c - 1
+    kf, vf = (torch.cat([r[:, prev], t], dim=1).cpu() for r, t in ((rk, k), (rv, v)))
+    o_ref, l_ref = run_oracle(q.cpu(), kf, vf, L, 1, W, scale)
+    compare(to_np(outs[0][0][:1]), to_np(outs[0][1][:1]), o_ref, l_ref, label=f"low items ring d={d} bh={bh}")
+
+
 @pytest.mark.parametrize("d,L", [(128, 260), (64, 264)])
 def test_half_items_ring_step(dev, d, L):
     """The ring step with 128-row items, whose key tiles straddle two slots, against
