@@ -133,6 +133,14 @@ int main() {
     bwd_plan(gpu[i], 256, false, &p);
     CHECK(p.q_split == 1 && p.kv_split == 1);
   }
+  // more than four units per CU (tests/test_gpu_full_items.py: over 1024 heads): whole units
+  for (int i = 0; i < 40; ++i, ++cases) {
+    const int64_t L = pick(1, 700), nkv = pick(1, 1500), off = std::min<int64_t>(pick(0, 3), (nkv - 1) / std::min(L, nkv));
+    BwdPlan p;
+    bwd_plan(make(pick(1025, 1028), pick(1, nkv - off * std::min(L, nkv)), nkv, L, L > nkv ? 0 : off, pick(-1, 4)), 256,
+             true, &p);
+    CHECK(p.q_split == 1 && p.kv_split == 1);
+  }
   // the grouped schedule against CU-by-CU simulation
   for (int i = 0; i < 200; ++i, ++cases) {
     WorkClass cls[kMaxClasses];

@@ -2,9 +2,10 @@
 64 and 128, positive and negative scale).  The 480p shape (B=1, H=12, 6 chunks
 of 3120 tokens, 936 uneven items) is one the host packs into per-CU lists
 (tests/test_item_lists.py checks that plan on the CPU), while each chunk of it
-as a streaming call (156 items) keeps plain dispatch.  So: every row of the
-parallel call must equal the streaming calls bit for bit (the same items, run
-by the other kernel), and a stratified row sample must match the fp64 oracle."""
+as a streaming call (156 items of 256 rows) runs by plain dispatch, as 240 items
+of 160 rows.  So: every row of the parallel call must equal the streaming calls
+bit for bit (the same rows in other items, run by the other kernel), and a
+stratified row sample must match the fp64 oracle."""
 import numpy as np
 import pytest
 import torch

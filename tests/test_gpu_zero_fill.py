@@ -12,12 +12,14 @@ in the other; every access stays inside the allocation either way.  The
 outputs of the two runs must be identical bit for bit, finite, and (for the
 forward) within the parity bar of the fp64 oracle.
 
-Covered: the forward's plain kernel (parallel call with future keys; a
-streaming call on a KV cache whose rows past cache_len are poisoned, contiguous
-and batch-strided), the per-CU list kernel (a shape the host packs into lists,
-see tests/item_lists_check.cpp), the ring step (new chunk in a poisoned buffer,
-the slot being replaced poisoned), and both backward kernels (Q, dO, O, K, V and
-the row-statistics workspace with poisoned tails)."""
+Covered: the forward's 128-row items (calls this small; parallel call with
+future keys; a streaming call on a KV cache whose rows past cache_len are
+poisoned, contiguous and batch-strided), the per-CU list kernel (a shape the
+host packs into lists, see tests/item_lists_check.cpp), the ring step with
+128-row items (new chunk in a poisoned buffer, the slot being replaced
+poisoned), and the backward's dQ and dK/dV units (Q, dO, O, K, V and the
+row-statistics workspace with poisoned tails).  tests/test_gpu_full_items.py
+has the same cases on the 256-row kernels of large calls."""
 import numpy as np
 import pytest
 import torch
@@ -201,8 +203,8 @@ BWD_CASES = [
 @pytest.mark.parametrize("case", BWD_CASES, ids=[c[0] for c in BWD_CASES])
 def test_backward_poisoned_tails(dev, case):
     """Q, dO and O with NaN rows past Nq, K and V with NaN rows past Nkv, and the
-    row-statistics workspace with a NaN tail: the query tiles the dK/dV kernel
-    stages past Nq and the key tiles the dQ kernel stages past the interval
+    row-statistics workspace with a NaN tail: the query tiles the dK/dV units
+    stage past Nq and the key tiles the dQ units stage past the interval
     must read as zero."""
     name, H, d, nq, nkv, L, off, W = case
     _announce(f"zero-fill bwd {name} H={H} d={d} Nq={nq} Nkv={nkv} L={L} off={off} W={W}")
