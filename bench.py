@@ -233,9 +233,9 @@ def backward_1080p(torch, fastvr, metrics, dev, cur, qd, kd, vd, w, reps: int):
     f = 2.5 * metrics.effective_flops(w.B, w.H, w.d, w.n_tokens, w.n_tokens, w.chunk_len, 0, w.window_chunks)
     return {"ms": round(ms, 4), "tflops": round(f / (ms * 1e-3) / 1e12, 2),
             "frac_of_bf16_peak": round(f / (ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS, 4),
-            "note": "dQ, dK, dV of the parallel call given O and LSE (two kernels); effective flop = "
-                    "10 d per visible pair (5 products); the kernels execute 7 (S and dP are "
-                    "recomputed by both)"}
+            "note": "dQ, dK, dV of the parallel call given O and LSE (row statistics, then all gradients); "
+                    "effective flop = 10 d per visible pair (5 products); 7 are executed (S and dP by "
+                    "the dQ units and by the dK/dV units)"}
 
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E

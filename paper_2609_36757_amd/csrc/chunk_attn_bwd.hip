@@ -12,7 +12,10 @@
 //
 // Two launches.  The first (row statistics) writes LSE * log2 e and -D of every
 // query row to a workspace.  The second runs two kinds of work units side by
-// side, longest first (bwd_plan.h):
+// side, longest first (bwd_plan.h), so that a call has one idle end instead of
+// one per kind: 4.06 -> 3.77 ms (6 chunks of 3120 tokens, 12 heads, 2700 units),
+// 47.5 -> 18.9 us (4 x 256 tokens, 2 heads, with units cut in two).  With 7000
+// units that end weighs no more than the first launch: 18.56 -> 18.64 ms.
 //  * dQ units (query-stationary, the forward's grid): 8 waves, 32 queries each,
 //    Q and dO fragments in registers; per 64-key tile S^T = K Q^T and
 //    dP^T = V dO^T (one query per lane, 16 keys per lane), P^T and dS^T in
@@ -54,10 +57,10 @@ namespace {
 using namespace dev;
 
 #ifndef FASTVR_BWD_AHEAD
-#define FASTVR_BWD_AHEAD 4  // dK/dV kernel: MFMA operand reads kept in flight ahead (0: the compiler places them)
+#define FASTVR_BWD_AHEAD 4  // dK/dV units: MFMA operand reads kept in flight ahead (0: the compiler places them)
 #endif
 #ifndef FASTVR_DQ_AHEAD
-#define FASTVR_DQ_AHEAD 4  // dQ kernel: MFMA operand reads kept in flight ahead (0: the compiler places them)
+#define FASTVR_DQ_AHEAD 4  // dQ units: MFMA operand reads kept in flight ahead (0: the compiler places them)
 #endif
 #ifndef FASTVR_PRIO
 #define FASTVR_PRIO 1  // raise the wave priority during matrix-core slots
@@ -406,8 +409,9 @@ __device__ __forceinline__ void dq_unit(const BwdParams& p, int cl, int bh, int 
   // 16 registers are kept instead of rebuilt for every tile).  With the mask
   // kept to the last tile this takes the vector-ALU work per score from a
   // compare, a select, an fma, an exp2, a subtraction, a multiply and half a
-  // conversion to four of the seven: the whole backward 18.47 -> 18.22 ms
-  // (4 x 12288 tokens, 12 heads, W = 1), 51.8 -> 47.5 us (4 x 256, 2 heads, d = 64).
+  // conversion to four of the seven: the whole backward 18.80 -> 18.56 ms
+  // (4 x 12288 tokens, 12 heads, W = 1), 46.9 -> 46.3 ms (4 x 16320, 12 heads),
+  // 51.6 -> 47.5 us (4 x 256, 2 heads, d = 64), libraries timed in turn on one card.
   f32x16 neg_d;
 #pragma unroll
   for (int v = 0; v < 16; ++v) neg_d[v] = neg_dlt;
@@ -996,8 +1000,8 @@ hipError_t launch_chunk_attn_bwd(const BwdArgs& a, hipStream_t stream) {
 // the row statistics [B, H, 2, Nq] live in this array instead of caller
 // memory.  Each device holds its own copy from the first load of the library's
 // code object until the process ends; every call on a device shares it.  The
-// dQ kernel writes every entry the dK/dV kernel reads before it reads them
-// (same stream), so nothing has to start at zero.
+// row statistics kernel writes every entry before the gradient kernel, next on
+// the same stream, reads it, so nothing has to start at zero.
 static __device__ __align__(256) float scratch[kBwdScratchFloats];
 
 // Device address of this device's copy of `scratch` (host code must not use

@@ -895,12 +895,15 @@ __global__ __launch_bounds__(kFwdThreads) void chunk_attn_fwd_list_kernel(const 
 //
 // A key tile takes 1.28 us (head_dim 128) or 0.77 us (64) against 2.05 and 1.58 us
 // in a 256-row item on a chip that is not full: one chunk of 3000 tokens and 4
-// heads 71.6 -> 47.8 us, 4 x 256 tokens and 2 heads (d = 64) 23.4 -> 15.2 us.
-// At head_dim 128 the step is bound by LDS and the tile DMA: 240 KB of operand
-// and P traffic at 128 bytes per clock is 1900 cycles, and 12 DMA instructions
-// per O wave hold it for 1560 (giving the score waves half of K's, or either
-// role a higher priority, changed nothing); at 64 by the softmax of the score
-// wave.  Twice the K/V traffic per query row makes it 14% (11%) slower than
+// heads 71.6 -> 46.3 us, 4 x 256 tokens and 2 heads (d = 64) 23.4 -> 15.2 us.
+// No unit is full then: on its CU the matrix core is busy 37% and LDS 26% of the
+// time (head_dim 128; 23% and 26% at 64, 6% of it conflicts).  A step is as long
+// as two serial chains of about the same length, S and softmax in one wave,
+// 12 DMA instructions (130 cycles each) and P V in the other.  Leaving parts out,
+// for timing, of those 46.3 us: the DMA 45.3, the softmax 45.7, V's LDS reads
+// 43.2, all of P V 34.9; at head_dim 64, of 35.4 us: 35.6, 30.4, 32.4, 30.4.
+// (Giving the score waves half of K's DMA, or either role a higher priority,
+// changed nothing.)  Twice the K/V traffic per query row makes it 14% (11%) slower than
 // 256-row items on a full chip, so fwd_plan.h picks the height per call.
 static_assert(kHalfRows == 4 * 32, "32 rows per wave pair");
 

@@ -18,8 +18,8 @@ FwdGrid fwd_grid(int64_t B, int64_t H, int64_t nq, int64_t chunk_len) {
   return g;
 }
 
-// Backward: the dQ kernel uses the forward's items; the dK/dV kernel one item
-// per (batch, head, key chunk, block of kBwdKeysPerItem keys).
+// Backward: dQ units are the forward's 256-row items; dK/dV units one per (batch,
+// head, key chunk, block of kBwdKeysPerItem keys).  (The plan may cut them in two.)
 BwdGrid bwd_grid(int64_t B, int64_t H, int64_t nq, int64_t nkv, int64_t chunk_len) {
   BwdGrid g{};
   const int64_t L = chunk_len > nkv ? nkv : chunk_len;
