@@ -13,8 +13,8 @@
 //    axis weights, and the field is the weight-normalised sum over the tiles
 //    covering the position.  Optionally fused with the one-step update of
 //    Eq. 9: z_hat = z_LQ - sigma * blend(v tiles).
-// Both kernels are bound by HBM bandwidth.  The gather copies each tile row (a
-// contiguous run in source and destination) with 16-byte vectors; the blend
+// Both kernels are bound by HBM bandwidth.  The gather reads each 16-byte unit of
+// the field once and writes it to the tiles that hold it; the blend
 // gathers, for each output element, the few tiles covering it (no atomics), with
 // the covering tiles of a run of positions found in closed form.
 #include <hip/hip_runtime.h>
@@ -22,78 +22,58 @@
 
 #include "gfx950_ops.h"
 #include "launch.h"
+#include "tile_plan.h"
 
 namespace fastvr {
 namespace {
 
 using namespace dev;
 
-constexpr int kThreads = 256;
-
-struct Axis {
-  int n, L, span;  // tiles, tile length, size - L
-};
+constexpr int kThreads = kTileThreads;
 
 __device__ __forceinline__ int axis_weight(int i, int L, int R) {
   const int m = (i + 1 < L - i) ? i + 1 : L - i;
   return m < R ? m : R;
 }
 
-// Index arithmetic in type I: uint32_t when every numerator below
-// fits (the usual case), uint64_t otherwise.
-template <typename I>
-__device__ __forceinline__ int origin_t(const Axis& a, int k) {
-  return a.n == 1 ? 0 : (int)(((I)k * (I)a.span + (I)((a.n - 1) / 2)) / (I)(a.n - 1));
-}
-
-// Last tile starting at or before position p: the largest k with origin(k) <= p.
-// origin(k) <= p  <=>  k * span + (n - 1) / 2 < (p + 1)(n - 1), solved for k.
-template <typename I>
-__device__ __forceinline__ int last_start_le(const Axis& a, int p) {
-  if (a.n == 1) return 0;
-  const I num = (I)(p + 1) * (I)(a.n - 1) - (I)((a.n - 1) / 2) - 1;
-  const I k = num / (I)a.span;  // span > 0 whenever n > 1
-  return k < (I)(a.n - 1) ? (int)k : a.n - 1;
-}
-
-// First tile ending after position p: the smallest k with origin(k) + L > p,
-// i.e. one past the last tile starting at or before p - L.
-template <typename I>
-__device__ __forceinline__ int first_end_gt(const Axis& a, int p) {
-  const int m = p - a.L;
-  return m < 0 ? 0 : last_start_le<I>(a, m) + 1;
-}
-
-// Gather.  Work item = (field row r = (b * T + t) * Hg + y, segment of kThreads *
-// U consecutive 16-byte units of it).  A thread reads its U units (kThreads
-// apart) once and writes them to every tile that holds them; the tiles covering
+// Gather.  Work item = (field row r = (b * T + t) * Hg + y, segment of seg <= W * U
+// consecutive 16-byte units of it, part of its tiles), run by W threads: a wave or
+// the workgroup (tile_plan.h).  A thread reads its U units (W apart) once and
+// writes them to every tile of its part that holds them; the tiles covering
 // the row (along y) and the segment's positions (along x) are two index ranges
-// found in closed form.  A tile row is a contiguous run of the field row, so unit
-// u of the field row is unit u - ox * C16 of the tile row at origin ox.
+// found in closed form, of which part z of zy * zx takes every zy-th and zx-th.
+// A tile row is a contiguous run of the field row, so unit u of the field row is
+// unit u - ox * C16 of the tile row at origin ox.
 // Bound by the HBM writes: each field unit is read once from memory, where one
 // workgroup per tile row read every tile's share of it again.  6 tiles of 8 x 64 x
 // 64 x 1536 (604 MB written, 200 MB read) 175.6 -> 115.4 us, 7.0 TB/s; 2 x 12
 // tiles of 32 x 32 rows, 768 channels 82.8 -> 63.1 us; a single tile (a plain
 // copy) 18.5 -> 17.8 us.  Three units a thread: two were 5% slower on the single
 // tile, four 1 to 2% on many small tiles; field loads past the caches cost 20%.
-constexpr int kGatherUnits = 3;
-template <typename I>
+// STREAM: stores past the caches.  Not when the tiles of a place are shared among
+// workgroups: tile rows then start at any 16 bytes of a line, and the caches
+// put the lines together (100 x 100, 48 channels, tiles of 64 one position apart 132
+// -> 115 us; 304 x 75, 88 channels, tiles of 11 two apart 65 -> 39 us).
+template <typename I, int W, bool STREAM>
 __global__ __launch_bounds__(kThreads) void tile_gather_kernel(const u32x4* __restrict__ x, u32x4* __restrict__ tiles,
                                                                int T, int Hg, int Wg, int C16, Axis ay, Axis ax,
-                                                               int64_t n_rows) {
-  constexpr int U = kGatherUnits;
+                                                               int64_t n_rows, int seg, int zy, int zx) {
+  constexpr int U = kGatherUnits, kRows = kThreads / W;
   const int row_units = Wg * C16;
   const int tile_units = ax.L * C16;  // of one tile row
   const int nt = ay.n * ax.n;
   const int64_t tile_rows = (int64_t)T * ay.L;
-  const int u_begin = blockIdx.x * (kThreads * U);
-  const int u_end = min(u_begin + kThreads * U, row_units);
-  const int tx_lo = first_end_gt<I>(ax, u_begin / C16), tx_hi = last_start_le<I>(ax, (u_end - 1) / C16);
-  for (int64_t r = blockIdx.y; r < n_rows; r += gridDim.y) {
+  const int u_begin = blockIdx.x * seg;
+  const int u_end = min(u_begin + seg, row_units);
+  const int tx_hi = last_start_le<I>(ax, (u_end - 1) / C16);
+  const int ty_part = (int)blockIdx.z % zy, tx_lo = first_end_gt<I>(ax, u_begin / C16) + (int)blockIdx.z / zy;
+  // W >= 64: one row per wave
+  const int sub = W == kThreads ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.y);
+  for (int64_t r = (int64_t)blockIdx.y * kRows + sub; r < n_rows; r += (int64_t)gridDim.y * kRows) {
     u32x4 val[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-      const int u = u_begin + k * kThreads + (int)threadIdx.x;
+      const int u = u_begin + k * W + (int)threadIdx.x;
       if (u < u_end) val[k] = x[r * row_units + u];
     }
     const I rr = (I)r;
@@ -102,15 +82,20 @@ __global__ __launch_bounds__(kThreads) void tile_gather_kernel(const u32x4* __re
     const int t = (int)(bt % (I)T);
     const int64_t b = (int64_t)(bt / (I)T);
     const int ty_hi = last_start_le<I>(ay, y);
-    for (int ty = first_end_gt<I>(ay, y); ty <= ty_hi; ++ty) {
+    for (int ty = first_end_gt<I>(ay, y) + ty_part; ty <= ty_hi; ty += zy) {
       const int64_t row0 = ((b * nt + ty * ax.n) * T + t) * ay.L + (y - origin_t<I>(ay, ty));  // tile row for tx = 0
-      for (int tx = tx_lo; tx <= tx_hi; ++tx) {
+      for (int tx = tx_lo; tx <= tx_hi; tx += zx) {
         const int u0 = origin_t<I>(ax, tx) * C16;
         u32x4* dst = tiles + (row0 + (int64_t)tx * tile_rows) * tile_units;
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-          const int u = u_begin + k * kThreads + (int)threadIdx.x, v = u - u0;
-          if (u < u_end && v >= 0 && v < tile_units) __builtin_nontemporal_store(val[k], dst + v);
+          const int u = u_begin + k * W + (int)threadIdx.x, v = u - u0;
+          if (u < u_end && v >= 0 && v < tile_units) {
+            if (STREAM)
+              __builtin_nontemporal_store(val[k], dst + v);
+            else
+              dst[v] = val[k];
+          }
         }
       }
     }
@@ -230,15 +215,29 @@ hipError_t launch_tile_gather(const void* x, void* tiles, int64_t B, int64_t T, 
                               int64_t tile, int64_t overlap, hipStream_t stream) {
   const Axis ay = make_axis(Hg, tile, overlap), ax = make_axis(Wg, tile, overlap);
   const int64_t rows = B * T * Hg;
-  const dim3 grid = row_grid(Wg * (C / 8), rows, kGatherUnits);
+  const GatherGrid g = gather_grid(rows, Wg, C / 8, ay, ax);
+  const dim3 grid((unsigned)g.segments, (unsigned)g.row_groups, (unsigned)(g.zy * g.zx));
+  const dim3 block(g.width, kThreads / g.width);
   const u32x4* xp = static_cast<const u32x4*>(x);
   u32x4* tp = static_cast<u32x4*>(tiles);
-  if (narrow_index(rows, ay, ax, Hg, Wg))
-    hipLaunchKernelGGL(tile_gather_kernel<uint32_t>, grid, dim3(kThreads), 0, stream, xp, tp, (int)T, (int)Hg, (int)Wg,
-                       (int)(C / 8), ay, ax, rows);
-  else
-    hipLaunchKernelGGL(tile_gather_kernel<uint64_t>, grid, dim3(kThreads), 0, stream, xp, tp, (int)T, (int)Hg, (int)Wg,
-                       (int)(C / 8), ay, ax, rows);
+#define FASTVR_GATHER_LAUNCH(IT, WV, SV)                                                                             \
+  hipLaunchKernelGGL((tile_gather_kernel<IT, WV, SV>), grid, block, 0, stream, xp, tp, (int)T, (int)Hg, (int)Wg, \
+                     (int)(C / 8), ay, ax, rows, g.seg, g.zy, g.zx)
+#define FASTVR_GATHER_INDEX(WV, SV)                        \
+  do {                                                     \
+    if (narrow) FASTVR_GATHER_LAUNCH(uint32_t, WV, SV);    \
+    else FASTVR_GATHER_LAUNCH(uint64_t, WV, SV);           \
+  } while (0)
+  const bool narrow = narrow_index(rows, ay, ax, Hg, Wg), shared = g.zy * g.zx > 1;
+  if (g.width == 64) {
+    if (shared) FASTVR_GATHER_INDEX(64, false);
+    else FASTVR_GATHER_INDEX(64, true);
+  } else {
+    if (shared) FASTVR_GATHER_INDEX(kThreads, false);
+    else FASTVR_GATHER_INDEX(kThreads, true);
+  }
+#undef FASTVR_GATHER_INDEX
+#undef FASTVR_GATHER_LAUNCH
   return hipGetLastError();
 }
 

@@ -1,5 +1,6 @@
-"""The gather around the edges of its 768-unit segments and in grids of one tile,
-bit for bit against slicing; the blend of a tile tensor past the 320 MB line (four
+"""The gather around the edges of its segments, in grids of one tile, by a wave per
+row and by a workgroup, with the tiles of a place shared among workgroups (which
+shapes take which: tests/tile_plan_check.cpp), bit for bit against slicing; the blend of a tile tensor past the 320 MB line (four
 units a thread) bit for bit against the same field blended in pairs (two units)
 and one by one (at the 64 MB line, read through the caches)."""
 import pytest
@@ -21,7 +22,9 @@ def dev():
 
 # Hg, Wg, C, tile, overlap: one row is Wg * C / 8 units of 16 bytes
 @pytest.mark.parametrize("Hg,Wg,C,tile,overlap", [(5, 767, 8, 64, 16), (70, 768, 8, 64, 0), (5, 769, 8, 64, 16),
-                                                  (9, 11, 560, 64, 16), (33, 97, 64, 32, 31), (1, 1, 8, 1, 0)])
+                                                  (9, 11, 560, 64, 16), (33, 97, 64, 32, 31), (1, 1, 8, 1, 0),
+                                                  (40, 45, 384, 32, 30), (40, 45, 40, 32, 31), (30, 30, 16, 64, 16),
+                                                  (64, 100, 64, 64, 16), (13, 321, 8, 64, 16), (13, 41, 64, 40, 8)])
 def test_gather_equals_slices(dev, Hg, Wg, C, tile, overlap):
     B, T = 2, 3
     print(f"\n[gpu case] gather B={B} T={T} {Hg}x{Wg} C={C} tile={tile} overlap={overlap}", flush=True)
