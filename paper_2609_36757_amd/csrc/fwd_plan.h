@@ -29,7 +29,10 @@ struct FwdPlan {
 // Heights of a call whose 256-row items all run at once, on no more than the
 // CUs: the lowest that still does.  A CU's time falls a little with its rows
 // (156 items of 256 rows 280 us; 204 of 192 rows 267; 240 of 160 rows 263; fewer
-// waves at the LDS), and the CUs that had no item take the rest.
+// waves at the LDS), and the CUs that had no item take the rest.  It falls no
+// further because 160 rows are five 32-row waves on four SIMDs: the SIMD with two
+// of them needs as long for a key tile as with 256 rows, and the others, with one
+// wave each, leave their matrix cores idle in every second slot.
 constexpr int kLowHeights[] = {160, 192, 224};
 
 // Items per CU up to which 128-row items are considered.
