@@ -17,8 +17,9 @@
 // few per CU and uneven, the host instead packs them into one list per CU and
 // launches one workgroup per CU that runs its list (item_lists.h).
 // Each wave owns 32 query rows.  Scores are computed transposed, S^T = K Q^T, with
-// v_mfma_f32_32x32x16_bf16: the accumulator puts one query per lane (column) and 16 keys per lane (rows), so row max and row sum are in-lane
-// plus one exchange between the two 32-lane halves.  The same registers,
+// v_mfma_f32_32x32x16_bf16: the accumulator puts one query per lane (column) and
+// 16 keys per lane (rows), so row max and row sum are in-lane plus one exchange
+// between the two 32-lane halves.  The same registers,
 // rounded to bf16, are the B operand of O^T = V^T P^T.
 //
 // Matrix-core / vector-ALU ping-pong: waves 0-3 (group A) and 4-7 (group B)
