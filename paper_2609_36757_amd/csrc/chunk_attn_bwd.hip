@@ -409,9 +409,10 @@ __device__ __forceinline__ void dq_unit(const BwdParams& p, int cl, int bh, int 
   // 16 registers are kept instead of rebuilt for every tile).  With the mask
   // kept to the last tile this takes the vector-ALU work per score from a
   // compare, a select, an fma, an exp2, a subtraction, a multiply and half a
-  // conversion to four of the seven: the whole backward 18.80 -> 18.56 ms
-  // (4 x 12288 tokens, 12 heads, W = 1), 46.9 -> 46.3 ms (4 x 16320, 12 heads),
-  // 51.6 -> 47.5 us (4 x 256, 2 heads, d = 64), libraries timed in turn on one card.
+  // conversion to four of the seven: the whole backward 51.6 -> 47.5 us (4 x 256
+  // tokens, 2 heads, d = 64), 4.14 -> 4.06 ms (6 x 3120, 12 heads).  The largest calls,
+  // at the power limit, gain 1% on some cards (18.80 -> 18.56 ms, 4 x 12288, 12 heads,
+  // W = 1) and nothing on others.
   f32x16 neg_d;
 #pragma unroll
   for (int v = 0; v < 16; ++v) neg_d[v] = neg_dlt;
